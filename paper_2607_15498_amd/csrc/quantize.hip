@@ -29,40 +29,67 @@ __host__ __device__ constexpr uint32_t qz_tile_bytes(uint32_t m, int b) {
     return m == 0 ? 0u : 2u * ((m + 7u) & ~7u) * (uint32_t)b + 32u * ((m + 31u) / 32u);
 }
 
+// Chunk offsets: a thread takes one tile (one rank byte) per pass, all of a pass's loads
+// independent, and the 16 lanes of a chunk add up by a row reduction; the chunk sums of up to
+// QZ_SCAN_CHUNKS chunks then go through one scan.  Latency is all it costs: with one thread
+// walking 16 dependent rank loads per chunk it took 7.4 us at 30K tokens, now 4.5.
+constexpr int QZ_SCAN_CHUNKS = QZ_SCAN_THREADS;       // chunks per scan block
+
+// sum over the 16 lanes of a row, in every lane
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);   // row_ror:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, true);
+    return v;
+}
+// inclusive sum over the lanes of a row up to this one
+__device__ __forceinline__ uint32_t row_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1, zeros shifted in
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    return v;
+}
+
 __global__ __launch_bounds__(QZ_SCAN_THREADS) void qz_scan_kernel(const uint8_t* __restrict__ srank,
                                                                   int64_t N, int n_chunks, int bits,
                                                                   uint32_t* __restrict__ qchunk_off) {
-    __shared__ uint32_t part[QZ_SCAN_THREADS];
-    const int tid = threadIdx.x;
-    const int per = (n_chunks + QZ_SCAN_THREADS - 1) / QZ_SCAN_THREADS;   // chunks per thread
-    const int c0 = tid * per;
-    uint32_t sum = 0;
-    for (int c = c0; c < c0 + per && c < n_chunks; ++c) {
-        const int64_t t0 = (int64_t)c * CHUNK;
-        for (int h = 0; h < 16; ++h) {
-            const int64_t i = t0 + 16 * h;
-            if (i < N) sum += qz_tile_bytes(srank[i], bits);
+    __shared__ uint32_t part[QZ_SCAN_CHUNKS];
+    __shared__ uint32_t wsum[QZ_SCAN_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t base = 0;                                   // bytes of the scan blocks before
+    for (int cb = 0; cb < n_chunks; cb += QZ_SCAN_CHUNKS) {
+        const int nc = min(QZ_SCAN_CHUNKS, n_chunks - cb);
+#pragma unroll 4
+        for (int k = 0; k < 16; ++k) {
+            const int tile = QZ_SCAN_THREADS * k + tid;  // of this block; 16 tiles per chunk
+            const int64_t i = 16 * ((int64_t)16 * cb + tile);
+            const uint32_t b = row_sum(i < N ? qz_tile_bytes(srank[i], bits) : 0u);
+            if ((lane & 15) == 0) part[tile >> 4] = b;   // chunks past the last one: 0
+            if (QZ_SCAN_THREADS * (k + 1) >= 16 * nc) break;
         }
-    }
-    part[tid] = sum;
-    __syncthreads();
-    // inclusive scan over the threads (Hillis-Steele)
-    for (int off = 1; off < QZ_SCAN_THREADS; off <<= 1) {
-        const uint32_t v = tid >= off ? part[tid - off] : 0u;
         __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    uint32_t run = tid ? part[tid - 1] : 0u;
-    for (int c = c0; c < c0 + per && c < n_chunks; ++c) {
-        qchunk_off[c] = run;
-        const int64_t t0 = (int64_t)c * CHUNK;
-        for (int h = 0; h < 16; ++h) {
-            const int64_t i = t0 + 16 * h;
-            if (i < N) run += qz_tile_bytes(srank[i], bits);
+        const uint32_t own = tid < nc ? part[tid] : 0u;
+        uint32_t v = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)v, off, 64);
+            if (lane >= off) v += o;
         }
+        if (lane == 63) wsum[wave] = v;
+        __syncthreads();
+        uint32_t before = base, all = base;
+#pragma unroll
+        for (int w = 0; w < QZ_SCAN_THREADS / 64; ++w) {
+            before += w < wave ? wsum[w] : 0u;
+            all += wsum[w];
+        }
+        if (tid < nc) qchunk_off[cb + tid] = before + v - own;
+        base = all;
+        __syncthreads();                                 // part and wsum are reused
     }
-    if (tid == QZ_SCAN_THREADS - 1) qchunk_off[n_chunks] = part[tid];
+    if (tid == 0) qchunk_off[n_chunks] = base;
 }
 
 struct QzParams {
@@ -75,39 +102,85 @@ struct QzParams {
     int G, bits;
 };
 
-// One workgroup per (chunk, head, stream), its wave w taking tiles w, w + 4, w + 8, w + 12:
-// the chunk's tile sizes are loaded once per wave and each tile runs in four steps that only the wave's own lanes share (its own LDS region,
-// wave-scope fences): the bf16 tile rectangle into LDS, the 16 x KS group scales, every code
-// (int8, [position][coordinate] for both streams), the packed dwords (each assembled by one
-// lane from the fields it covers).  Element indices of a tile of size m are split into
-// (row, column) by a float reciprocal: for f < 2048 and m <= 128, floor(f * (1/m) + 2^-10)
-// is floor(f / m) exactly (the product errs by far less than 2^-10 and the fraction of f / m
-// is at most 127/128 below an integer).
+// One workgroup per (chunk, head, stream), its wave w taking tiles w, w + 4, w + 8, w + 12.
+// A wave quantises one 32-coordinate segment of a tile (16 positions x 32 coordinates, 1 KB of
+// bf16) per step, straight from registers: 8 coefficients per lane, of one group in the K
+// stream (position lane / 4, coordinates 8 (lane % 4) ..) and of one coordinate in the V
+// stream (coordinate lane / 2, positions 8 (lane % 2) ..), which is how either stream stores
+// them.  The first segments of all four tiles are requested before the first is used and a
+// tile's next segment before its current one, so the step is bound by its VALU work: about 9
+// instructions per coefficient (staging the tile and its codes in LDS, with a row / column
+// split and a full division per element, took 75 us for the 29987-token layer where this
+// takes 18).
+//
+// Arithmetic.  Absolute bf16 values order as their 15-bit patterns do, so a group's absmax is
+// a packed integer maximum.  Both divisions are a product with a reciprocal and one residual
+// correction.  amax / Qmax: the reciprocal is the constant's nearest fp32 value, so the
+// corrected quotient is correctly rounded.  x / scale, for |x| <= amax with an 8-bit
+// significand and a scale with at most 11 bits: a quotient that is not exactly half-way between
+// two integers is at least 2^-12 away from it, far more than the error, and one that is
+// exactly half-way comes out exact, so the rounding to an integer (the addition of
+// 1.5 * 2^23, ties to even) agrees with that of the correctly rounded quotient.  Groups whose
+// scale is not finite (absmax above the binary16 range, infinities, NaN) take the plain
+// divisions.
 constexpr int QZ_WAVES = 4;
-constexpr int QZ_VS = D + 1;                      // padded LDS row stride: no bank conflicts
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+__device__ __forceinline__ uint32_t qz_umax2(uint32_t a, uint32_t b) {     // packed 16-bit maxima
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 x = __builtin_bit_cast(u16x2, a), y = __builtin_bit_cast(u16x2, b);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(x, y));
 }
-
-__device__ __forceinline__ int qz_div(int f, float inv) { return (int)(fmaf((float)f, inv, 0.0009765625f)); }
+template <int CTRL> __device__ __forceinline__ uint32_t qz_dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+// binary16 scale of a group from its absmax (finite)
+template <int QB> __device__ __forceinline__ _Float16 qz_scale(float amax) {
+    constexpr float Q = (float)((1 << (QB - 1)) - 1), RQ = 1.0f / Q;
+    const float q = amax * RQ;
+    return (_Float16)fmaf(fmaf(-q, Q, amax), RQ, q);
+}
+// code of x at scale sc with rc = 1 / sc (both 0 for a zero group), in the low bits
+template <int QB> __device__ __forceinline__ uint32_t qz_code(float x, float sc, float rc) {
+    constexpr float Q = (float)((1 << (QB - 1)) - 1);
+    const float q0 = x * rc;
+    const float q = fmaf(fmaf(-q0, sc, x), rc, q0);
+    return __float_as_uint(__builtin_amdgcn_fmed3f(q, -Q, Q) + 12582912.f);
+}
+// the same by the plain divisions (any sc)
+template <int QB> __device__ __forceinline__ uint32_t qz_code_any(float x, float sc) {
+    constexpr float Q = (float)((1 << (QB - 1)) - 1);
+    if (sc == 0.f) return 0u;
+    return (uint32_t)(int)fminf(fmaxf(__builtin_rintf(__fdiv_rn(x, sc)), -Q), Q);
+}
+// 8 codes (low bits of c[k]) -> 8 QB bits at dst (any byte address)
+template <int QB> __device__ __forceinline__ void qz_store(uint8_t* dst, const uint32_t (&c)[8]) {
+    if constexpr (QB == 8) {
+        uint32_t w[2] = {0u, 0u};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k >> 2] = __builtin_amdgcn_alignbit(c[k], w[k >> 2], 8);
+        *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
+    } else {
+        uint32_t w = 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w = __builtin_amdgcn_alignbit(c[k], w, QB);
+        if constexpr (QB == 4) {
+            *reinterpret_cast<uint32_t*>(dst) = w;
+        } else {
+            w >>= 8;
+            dst[0] = (uint8_t)w;
+            dst[1] = (uint8_t)(w >> 8);
+            dst[2] = (uint8_t)(w >> 16);
+        }
+    }
+}
 
 template <int QB>
 __global__ __launch_bounds__(64 * QZ_WAVES) void qz_kernel(QzParams p, int total) {
-    constexpr int QMAX = (1 << (QB - 1)) - 1;
-    constexpr int VS = QZ_VS;
-    __shared__ float val_s[QZ_WAVES][16 * VS];    // tile values, [position][coordinate]
-    __shared__ float scl_s[QZ_WAVES][4 * 16];     // [group][position]
-    __shared__ uint16_t sclh_s[QZ_WAVES][4 * 16]; // the same as binary16 bits
-    __shared__ int8_t cod_s[QZ_WAVES][16 * VS];   // codes, [position][coordinate]
-    const int wave = threadIdx.x >> 6, tid = threadIdx.x & 63;
-    float* val = val_s[wave];
-    float* scl = scl_s[wave];
-    uint16_t* sclh = sclh_s[wave];
-    int8_t* cod = cod_s[wave];
-    const int item = blockIdx.x;                  // (chunk, head, stream); wave w takes tiles w, w + 4, ...
+    constexpr int NT = 16 / QZ_WAVES;             // tiles per wave
+    constexpr uint32_t INF16 = 0x7F80u;           // bf16 infinity's pattern
+    __shared__ __attribute__((aligned(16))) float scl_s[QZ_WAVES][2][16];   // V: scales, reciprocals
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int item = blockIdx.x;                  // (chunk, head, stream)
     if (item >= total) return;
     const int kv = item & 1;
     const int g = (item >> 1) % p.G;
@@ -115,100 +188,127 @@ __global__ __launch_bounds__(64 * QZ_WAVES) void qz_kernel(QzParams p, int total
     const int64_t t0 = (int64_t)c * CHUNK;
     const int T = (int)(p.N - t0 < CHUNK ? p.N - t0 : CHUNK);
     const int ntile = (T + 15) >> 4;
-    // the chunk's tile sizes (lane h < 16 holds tile h's) and their prefix offsets
-    const uint32_t mlane = tid < ntile ? (uint32_t)p.srank[t0 + 16 * tid] : 0u;
-    uint32_t eo = p.chunk_off[c], bo = p.qchunk_off[c];
-    const uint16_t* base_src = p.coef[kv] + (int64_t)g * p.coef_stride;
-    uint8_t* base_dst = p.code[kv] + (int64_t)g * p.q_stride;
-    for (int h = 0; h < wave; ++h) {
-        const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)mlane, h);
-        eo += 16u * m;
-        bo += qz_tile_bytes(m, QB);
+    // lane h < 16: tile h's size and its offsets within the chunk (absent tiles: size 0)
+    const uint32_t mlane = (lane & 15) < ntile ? (uint32_t)p.srank[t0 + 16 * (lane & 15)] : 0u;
+    const uint32_t eo = row_scan(16u * mlane) - 16u * mlane;
+    const uint32_t tb = qz_tile_bytes(mlane, QB);
+    const uint32_t bo = row_scan(tb) - tb;
+    const uint16_t* base_src = p.coef[kv] + (int64_t)g * p.coef_stride + p.chunk_off[c];
+    uint8_t* base_dst = p.code[kv] + (int64_t)g * p.q_stride + p.qchunk_off[c];
+    // this lane's 8 coefficients of segment s of a tile of size m (zeros past the tile)
+    auto fetch = [&](const uint16_t* src, int m, int s) -> u32x4 {
+        if (kv == 0) {
+            const int j = 32 * s + 8 * (lane & 3);
+            if (j >= m) return u32x4{0u, 0u, 0u, 0u};
+            return load16_a2(src + (lane >> 2) * m + j);     // may run past the row: masked below
+        }
+        if (32 * s + (lane >> 1) >= m) return u32x4{0u, 0u, 0u, 0u};
+        return load16(src + 512 * s + 8 * lane);
+    };
+    int mt[NT];
+    u32x4 first[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+        const int h = wave + QZ_WAVES * k;
+        mt[k] = __builtin_amdgcn_readlane((int)mlane, h);
+        first[k] = fetch(base_src + __builtin_amdgcn_readlane((int)eo, h), mt[k], 0);
     }
-    for (int h = wave; h < ntile; h += QZ_WAVES) {
-        const int mt = __builtin_amdgcn_readlane((int)mlane, h);
-        const int mq = (mt + 7) & ~7, ks = (mt + 31) / 32;
-        const uint16_t* src = base_src + eo;
-        uint8_t* dst = base_dst + bo;
-        // the offsets of this wave's next tile: past tiles h .. h + 3
-        for (int k = h; k < h + QZ_WAVES && k < ntile; ++k) {
-            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)mlane, k);
-            eo += 16u * m;
-            bo += qz_tile_bytes(m, QB);
-        }
-        const float inv_mt = 1.0f / (float)(mt > 0 ? mt : 1), inv_mq = 1.0f / (float)(mq > 0 ? mq : 1);
-        // ---- 1. the tile rectangle (16 mt contiguous bf16: K rows of mt, or V rows of 16),
-        //          16-byte loads scattered to [position][coordinate]; zeros up to mq
-        for (int e8 = tid; e8 < 2 * mt; e8 += 64) {
-            const u32x4 w = *reinterpret_cast<const u32x4*>(src + 8 * e8);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int f = 8 * e8 + k;
-                int i, j;
-                if (kv == 0) { i = qz_div(f, inv_mt); j = f - i * mt; }
-                else { j = f >> 4; i = f & 15; }
-                val[i * VS + j] = (k & 1) ? bf_hi(w[k >> 1]) : bf_lo(w[k >> 1]);
+    for (int k = 0; k < NT; ++k) {
+        const int h = wave + QZ_WAVES * k, m = mt[k];
+        const int mq = (m + 7) & ~7, ks = (m + 31) / 32;
+        const uint16_t* src = base_src + __builtin_amdgcn_readlane((int)eo, h);
+        uint8_t* dst = base_dst + __builtin_amdgcn_readlane((int)bo, h);
+        uint16_t* sdst = reinterpret_cast<uint16_t*>(dst + 2 * mq * QB);
+        u32x4 next = first[k];
+        for (int s = 0; s < ks; ++s) {
+            u32x4 x = next;
+            if (s + 1 < ks) next = fetch(src, m, s + 1);
+            uint32_t code[8];
+            if (kv == 0) {
+                const int i = lane >> 2, j = 32 * s + 8 * (lane & 3);
+                const int nv = m - j;
+                x = keep_first(x, nv < 0 ? 0 : (nv > 8 ? 8 : nv));
+                const u32x4 ab = x & 0x7FFF7FFFu;
+                uint32_t mx = qz_umax2(qz_umax2(ab[0], ab[1]), qz_umax2(ab[2], ab[3]));
+                mx = qz_umax2(mx, mx >> 16) & 0xFFFFu;
+                mx = max(mx, qz_dpp<0xB1>(mx));              // quad_perm [1,0,3,2]
+                mx = max(mx, qz_dpp<0x4E>(mx));              // quad_perm [2,3,0,1]
+                _Float16 hs = qz_scale<QB>(__uint_as_float(mx << 16));
+                const bool odd = mx >= INF16 || (float)hs == INFINITY;
+                if (__builtin_amdgcn_ballot_w64(odd) == 0) {
+                    const float sc = (float)hs, rc = sc != 0.f ? __builtin_amdgcn_rcpf(sc) : 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) code[e] = qz_code<QB>((e & 1) ? bf_hi(x[e >> 1]) : bf_lo(x[e >> 1]), sc, rc);
+                } else {
+                    float amax = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((e & 1) ? bf_hi(x[e >> 1]) : bf_lo(x[e >> 1])));
+                    amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
+                    amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
+                    hs = (_Float16)__fdiv_rn(amax, (float)((1 << (QB - 1)) - 1));
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        code[e] = qz_code_any<QB>((e & 1) ? bf_hi(x[e >> 1]) : bf_lo(x[e >> 1]), (float)hs);
+                }
+                if (j < mq) qz_store<QB>(dst + (i * mq + j) / 8 * QB, code);
+                if ((lane & 3) == 0) sdst[16 * s + i] = __builtin_bit_cast(uint16_t, hs);
+            } else {
+                // absmax of the lane's 8 positions over the 32 coordinates (the lanes of its
+                // parity): the two swaps halve what a lane holds, so it ends with the dword
+                // (two positions) 2 (lane / 32) + (lane / 16) % 2 of its parity's four
+                const u32x4 ab = x & 0x7FFF7FFFu;
+                const auto e0 = __builtin_amdgcn_permlane32_swap(ab[0], ab[2], false, false);
+                const auto e1 = __builtin_amdgcn_permlane32_swap(ab[1], ab[3], false, false);
+                const auto e2 = __builtin_amdgcn_permlane16_swap(qz_umax2(e0[0], e0[1]), qz_umax2(e1[0], e1[1]), false, false);
+                uint32_t mx = qz_umax2(e2[0], e2[1]);
+                mx = qz_umax2(mx, qz_dpp<0x128>(mx));        // row_ror: 8, 4, 2
+                mx = qz_umax2(mx, qz_dpp<0x124>(mx));
+                mx = qz_umax2(mx, qz_dpp<0x122>(mx));
+                const int p0 = 8 * (lane & 1) + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);
+                _Float16 h0 = qz_scale<QB>(__uint_as_float(mx << 16)), h1 = qz_scale<QB>(__uint_as_float(mx & 0xFFFF0000u));
+                const bool odd = (mx & 0xFFFFu) >= INF16 || (mx >> 16) >= INF16 || (float)h0 == INFINITY || (float)h1 == INFINITY;
+                const bool plain = __builtin_amdgcn_ballot_w64(odd) == 0;
+                float* scl = scl_s[wave][0];
+                float* rcp = scl_s[wave][1];
+                if (plain) {
+                    if ((lane & 14) == 0) {
+                        const float s0 = (float)h0, s1 = (float)h1;
+                        *reinterpret_cast<float2*>(scl + p0) = make_float2(s0, s1);
+                        *reinterpret_cast<float2*>(rcp + p0) = make_float2(s0 != 0.f ? __builtin_amdgcn_rcpf(s0) : 0.f,
+                                                                           s1 != 0.f ? __builtin_amdgcn_rcpf(s1) : 0.f);
+                        *reinterpret_cast<uint32_t*>(sdst + 16 * s + p0) =
+                            pack2(__builtin_bit_cast(uint16_t, h0), __builtin_bit_cast(uint16_t, h1));
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    f32x4 sc[2], rc[2];
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        sc[q] = *reinterpret_cast<const f32x4*>(scl + 8 * (lane & 1) + 4 * q);
+                        rc[q] = *reinterpret_cast<const f32x4*>(rcp + 8 * (lane & 1) + 4 * q);
+                    }
+                    __builtin_amdgcn_wave_barrier();         // the next step writes them again
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        code[e] = qz_code<QB>((e & 1) ? bf_hi(x[e >> 1]) : bf_lo(x[e >> 1]), sc[e >> 2][e & 3], rc[e >> 2][e & 3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float v = (e & 1) ? bf_hi(x[e >> 1]) : bf_lo(x[e >> 1]);
+                        float amax = fmaxf(0.f, fabsf(v));
+#pragma unroll
+                        for (int off = 2; off < 64; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+                        const _Float16 hs = (_Float16)__fdiv_rn(amax, (float)((1 << (QB - 1)) - 1));
+                        code[e] = qz_code_any<QB>(v, (float)hs);
+                        if (lane < 2) sdst[16 * s + 8 * lane + e] = __builtin_bit_cast(uint16_t, hs);
+                    }
+                }
+                const int j = 32 * s + (lane >> 1);
+                if (j < mq) qz_store<QB>(dst + (16 * j + 8 * (lane & 1)) / 8 * QB, code);
             }
         }
-        for (int e = tid; e < 16 * (mq - mt); e += 64) val[(e & 15) * VS + mt + (e >> 4)] = 0.f;
-        wave_sync();
-        // ---- 2. group scales: lane -> (group s, position i)
-        if (tid < 16 * ks) {
-            const int s = tid >> 4, i = tid & 15;
-            float a[32];
-#pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                const int j = 32 * s + u;
-                a[u] = j < mq ? fabsf(val[i * VS + j]) : 0.f;
-            }
-            float amax = 0.f;
-#pragma unroll
-            for (int u = 0; u < 32; ++u) amax = fmaxf(amax, a[u]);
-            const _Float16 hs = (_Float16)__fdiv_rn(amax, (float)QMAX);   // nearest binary16
-            scl[tid] = (float)hs;
-            sclh[tid] = __builtin_bit_cast(uint16_t, hs);
-        }
-        wave_sync();
-        // ---- 3. codes: element e -> position e & 15, coordinate e >> 4 (every lane busy)
-        for (int e = tid; e < 16 * mq; e += 64) {
-            const int i = e & 15, j = e >> 4;
-            const float sc = scl[16 * (j >> 5) + i];
-            int k = 0;
-            if (sc != 0.f) {
-                const float r = __builtin_rintf(__fdiv_rn(val[i * VS + j], sc));
-                k = (int)fminf(fmaxf(r, (float)-QMAX), (float)QMAX);
-            }
-            cod[i * VS + j] = (int8_t)k;
-        }
-        wave_sync();
-        // ---- 4. packed dwords: K code (i, j) is field i mq + j, V code (j, i) is field
-        //          16 j + i; then the scales
-        uint32_t* dw = reinterpret_cast<uint32_t*>(dst);      // tile start: 16-byte aligned
-        const int nd = mq * QB / 2;
-        constexpr int NF = (32 + QB - 1) / QB + 1;          // fields a dword can touch
-        for (int d = tid; d < nd; d += 64) {
-            uint32_t word = 0;
-            const int ebeg = (32 * d) / QB, eend = (32 * d + 31) / QB;
-            int8_t cv[NF];
-#pragma unroll
-            for (int u = 0; u < NF; ++u) {
-                const int ee = ebeg + u <= eend ? ebeg + u : ebeg;   // in bounds; dropped below
-                int i, j;
-                if (kv == 0) { i = qz_div(ee, inv_mq); j = ee - i * mq; }
-                else { j = ee >> 4; i = ee & 15; }
-                cv[u] = cod[i * VS + j];
-            }
-#pragma unroll
-            for (int u = 0; u < NF; ++u) {
-                const int ee = ebeg + u;
-                const uint32_t field = ee <= eend ? (uint32_t)(int)cv[u] & ((1u << QB) - 1u) : 0u;
-                const int sh = QB * ee - 32 * d;
-                word |= sh >= 0 ? (field << sh) : (field >> -sh);
-            }
-            dw[d] = word;
-        }
-        if (tid < 8 * ks) dw[nd + tid] = (uint32_t)sclh[2 * tid] | ((uint32_t)sclh[2 * tid + 1] << 16);
-        wave_sync();                              // the wave's LDS is reused by its next tile
     }
 }
 

@@ -272,3 +272,64 @@ def test_quantised_end_to_end(vr, oracle_lib, bits):
                                                    li.q[i], cfg["H"])) for i in range(2))
     say(f"[quantised end-to-end] bits={bits}: worst rel err {worst:.3e}")
     assert worst <= DEC_TOL_BF16
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+@pytest.mark.parametrize("N,top", [(1, 128), (17, 33), (256, 128), (773, 128), (262144 + 300, 9)])
+def test_codes_of_extreme_values(vr, bits, N, top):
+    """Codes, scales and chunk offsets bit for bit where the quantiser's forms can part: whole,
+    half-way and tiny quotients, zero groups, scales past the binary16 range, the last tile of a
+    ragged chunk, more chunks than one scan block holds.  Reference: correctly rounded fp32
+    divisions in numpy on the same stored coefficients."""
+    import torch
+    G, w = 2 if N < 10000 else 1, 1
+    # the buffers' sizes come from a shape whose budget covers the ranks drawn here
+    shape = vr.Shape(n=N + w, G=G, H=G, w=w, r_min=0, kappa_pct=99 if top > 16 else 12, dtype="bf16")
+    cache, qc = vr.new_cache(shape), vr.new_qcache(shape, bits)
+    rng = np.random.default_rng(1000 * bits + N)
+    rank = rng.integers(0, top + 1, N)
+    rank[rng.random(N) < 0.1] = 0
+    rank[0] = top
+    cap = (shape.kappa_pct * shape.n * 128) // 100 - w * 128
+    while rank.sum() > cap:
+        rank = np.maximum(rank - 1, 0)
+    srank, sidx, chunk_off = layout(rank, N)
+    # bf16 values: a binade near one, whole multiples and odd halves of a power-of-two scale (ties),
+    # and by position some groups huge (scale past binary16), tiny (scale 0 or subnormal) or zero
+    coef = rng.standard_normal((N, G, 128)).astype(np.float32)
+    qmax = 2 ** (bits - 1) - 1
+    ties = rng.random(N) < 0.3
+    coef[ties] = rng.integers(-2 * qmax, 2 * qmax + 1, (int(ties.sum()), G, 128)) / 2.0
+    coef[ties, :, ::32] = qmax
+    coef[rng.random(N) < 0.05] *= 1e36
+    coef[rng.random(N) < 0.05] *= 3e-8
+    coef[rng.random(N) < 0.05] *= 1e-39
+    coef[rng.random(N) < 0.05] = 0.0
+    coef = torch.from_numpy(coef).to(torch.bfloat16).float().numpy()
+    streams = {k: pack(coef, srank, sidx, chunk_off, N, k, cache.coef_stride) for k in ("K", "V")}
+    cache.coef_k.copy_(streams["K"])
+    cache.coef_v.copy_(streams["V"])
+    cache.srank.copy_(torch.from_numpy(srank.astype(np.uint8)))
+    cache.sidx.copy_(torch.from_numpy(sidx.astype(np.int32)))
+    cache.chunk_off.copy_(torch.from_numpy(chunk_off.astype(np.int32)))
+    vr.quantize(shape, cache, bits, qcache=qc)
+    torch.cuda.synchronize()
+    # offsets
+    tile_m = np.zeros((len(chunk_off) - 1) * 16, np.int64)
+    tile_m[:(N + 15) // 16] = srank[::16]
+    nbytes = np.where(tile_m > 0, 2 * ((tile_m + 7) // 8 * 8) * bits + 32 * ((tile_m + 31) // 32), 0)
+    qoff = np.concatenate([[0], np.cumsum(nbytes.reshape(-1, 16).sum(1))])
+    assert np.array_equal(qc.qchunk_off.cpu().numpy().astype(np.int64), qoff)
+    codes, scales = {}, {}
+    for kind, st in (("K", qc.code_k), ("V", qc.code_v)):
+        codes[kind], scales[kind] = unpack_codes(st.cpu().numpy(), qoff, srank, sidx, N, kind, bits)
+    keep = np.arange(128)[None, None, :] < rank[:, None, None]
+    x = np.where(keep, coef, np.float32(0)).reshape(N, G, 4, 32)
+    with np.errstate(over="ignore", divide="ignore", invalid="ignore"):
+        sc = (np.abs(x).max(axis=3) / np.float32(qmax)).astype(np.float16).astype(np.float32)
+        k = np.rint((x / sc[..., None]).astype(np.float32))
+    k = np.clip(np.where(sc[..., None] == 0, 0, k), -qmax, qmax).astype(np.int64).reshape(N, G, 128)
+    used = (np.arange(4)[None, :] * 32 < rank[:, None])[:, None, :]
+    for kind in ("K", "V"):
+        assert np.array_equal(codes[kind], k), kind
+        assert np.array_equal(np.where(used, scales[kind], 0), np.where(used, sc, 0)), kind
