@@ -874,7 +874,8 @@ __global__ __launch_bounds__(AK_T) void al_final(int64_t N, const uint32_t* __re
                                                  const uint64_t* __restrict__ phi_ws,
                                                  const uint64_t* __restrict__ cand, RT* __restrict__ rank,
                                                  uint8_t* __restrict__ srank, uint32_t* __restrict__ sidx,
-                                                 uint32_t* __restrict__ csum, const AlCtl* __restrict__ ctl) {
+                                                 uint32_t* __restrict__ csum, const AlCtl* __restrict__ ctl,
+                                                 uint4* __restrict__ ccnt) {
     __shared__ AlSelSmem ss;
     // storage order of each wave's chunk: per-rank 256-bit token masks, and the count of
     // tokens of higher rank per rank value
@@ -918,6 +919,18 @@ __global__ __launch_bounds__(AK_T) void al_final(int64_t N, const uint32_t* __re
         for (int k = 0; k < AK_PER; ++k)
             if (al_tok(k) < N) sum += r[k];
         size = wave_sum(sum);
+        if (ccnt) {                          // the chunk's tokens of rank above 0, 128, .. 896
+            uint32_t n8[4];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                uint32_t n = 0;
+#pragma unroll
+                for (int k = 0; k < AK_PER; ++k)
+                    n += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(al_tok(k) < N && r[k] > 128u * b));
+                n8[b >> 1] = (b & 1) ? n8[b >> 1] | (n << 16) : n;
+            }
+            if (lane == 0 && c * CHUNK < N) ccnt[c] = make_uint4(n8[0], n8[1], n8[2], n8[3]);
+        }
     }
     if (lane == 0 && c * CHUNK < N) csum[c] = size;
 }
@@ -941,16 +954,31 @@ __device__ __forceinline__ uint32_t chunk_prefix(const uint32_t* __restrict__ cs
 }
 
 // ---- 7. shared basis: chunk offsets and per-token offsets = chunk offset + the chunk's
-//         earlier ranks (one wave per chunk, which scans the chunk sums before it itself)
+//         earlier ranks (one wave per chunk, which scans the chunk sums before it itself).  With
+//         lists: the chunk's tokens of rank above 128 b join list b behind those of earlier chunks
 __global__ __launch_bounds__(AK_T) void al_offsets(int64_t N, const uint16_t* __restrict__ rank,
                                                    const uint32_t* __restrict__ csum,
                                                    uint32_t* __restrict__ chunk_off,
-                                                   uint32_t* __restrict__ offset, int n_chunks) {
+                                                   uint32_t* __restrict__ offset, int n_chunks,
+                                                   JointLists lists) {
     const int lane = threadIdx.x & 63;
     const int64_t c = (int64_t)blockIdx.x * (AK_TOK / CHUNK) + (threadIdx.x >> 6);
     if (c * CHUNK >= N) return;
     uint32_t pre = chunk_prefix(csum, c);
     if (lane == 0) chunk_off[c] = pre;
+    uint32_t lp[8] = {0, 0, 0, 0, 0, 0, 0, 0};             // list positions of the chunk's first tokens
+    if (lists.list) {
+#pragma unroll 4
+        for (int64_t i = lane; i < c; i += 64) {
+            const uint4 v = lists.ccnt[i];
+            lp[0] += v.x & 0xFFFFu; lp[1] += v.x >> 16;
+            lp[2] += v.y & 0xFFFFu; lp[3] += v.y >> 16;
+            lp[4] += v.z & 0xFFFFu; lp[5] += v.z >> 16;
+            lp[6] += v.w & 0xFFFFu; lp[7] += v.w >> 16;
+        }
+#pragma unroll
+        for (int b = 0; b < 8; ++b) lp[b] = wave_sum(lp[b]);
+    }
 #pragma unroll
     for (int k = 0; k < AK_PER; ++k) {
         const int64_t t = c * CHUNK + 64 * k + lane;       // the wave's tokens, in index order
@@ -963,10 +991,24 @@ __global__ __launch_bounds__(AK_T) void al_offsets(int64_t N, const uint16_t* __
         }
         if (t < N) offset[t] = pre + x - r;
         pre += __shfl(x, 63, 64);
+        if (lists.list) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                if (b >= lists.nb) break;
+                const bool in = r > 128u * b;
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+                if (in) lists.list[(int64_t)b * N + lp[b] + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)t;
+                lp[b] += (uint32_t)__popcll(m);
+            }
+        }
     }
     if (c == n_chunks - 1 && lane == 0) {       // the totals
         chunk_off[n_chunks] = pre;
         offset[N] = pre;
+        if (lists.list)
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                if (b < lists.nb) lists.list_n[b] = lp[b];
     }
 }
 
@@ -1015,7 +1057,8 @@ hipError_t launch_allocate(const varrate_shape& sh, const float* sbar, varrate_c
     al_fine<<<nwg, AW_T, 0, st>>>(N, B, r_min, R, w.u, w.c_pack, w.f_cnt, w.ctl);
     al_floors<uint8_t><<<nwg, AW_T, 0, st>>>(N, B, r_min, R, w.u, w.f_cnt, c.rank, w.phi, w.d_cnt, w.ctl);
     al_gather<<<nwg, AK_T, 0, st>>>(N, B, w.u, w.phi, w.d_cnt, w.cand, w.ctl);
-    al_final<uint8_t, true><<<nwg, AK_T, 0, st>>>(N, w.u, w.phi, w.cand, c.rank, c.srank, c.sidx, w.csum, w.ctl);
+    al_final<uint8_t, true><<<nwg, AK_T, 0, st>>>(N, w.u, w.phi, w.cand, c.rank, c.srank, c.sidx, w.csum, w.ctl,
+                                                nullptr);
     if (chunk_sizes)
         *chunk_sizes = w.csum;
     else
@@ -1025,7 +1068,7 @@ hipError_t launch_allocate(const varrate_shape& sh, const float* sbar, varrate_c
 
 hipError_t launch_allocate_joint(const varrate_shape& sh, int R, int64_t B, const float* sbar, uint16_t* rank,
                                  uint32_t* offset, uint32_t* chunk_off, uint8_t* ws, hipStream_t st,
-                                 const float* s_part) {
+                                 const float* s_part, const JointLists& lists) {
     const int64_t N = sh.n - sh.w;
     const int r_min = sh.r_min;
     const int nwg = (int)((N + AK_TOK - 1) / AK_TOK);
@@ -1041,8 +1084,9 @@ hipError_t launch_allocate_joint(const varrate_shape& sh, int R, int64_t B, cons
     al_fine<<<nwg, AW_T, 0, st>>>(N, B, r_min, R, w.u, w.c_pack, w.f_cnt, w.ctl);
     al_floors<uint16_t><<<nwg, AW_T, 0, st>>>(N, B, r_min, R, w.u, w.f_cnt, rank, w.phi, w.d_cnt, w.ctl);
     al_gather<<<nwg, AK_T, 0, st>>>(N, B, w.u, w.phi, w.d_cnt, w.cand, w.ctl);
-    al_final<uint16_t, false><<<nwg, AK_T, 0, st>>>(N, w.u, w.phi, w.cand, rank, nullptr, nullptr, w.csum, w.ctl);
-    al_offsets<<<nwg, AK_T, 0, st>>>(N, rank, w.csum, chunk_off, offset, n_chunks);
+    al_final<uint16_t, false><<<nwg, AK_T, 0, st>>>(N, w.u, w.phi, w.cand, rank, nullptr, nullptr, w.csum, w.ctl,
+                                                  lists.ccnt);
+    al_offsets<<<nwg, AK_T, 0, st>>>(N, rank, w.csum, chunk_off, offset, n_chunks, lists);
     return hipGetLastError();
 }
 

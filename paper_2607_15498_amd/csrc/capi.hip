@@ -512,7 +512,7 @@ int varrate_jcache_bytes(const varrate_shape* sh, int32_t R, int64_t cap, varrat
 
 size_t varrate_joint_compress_workspace_bytes(const varrate_shape* sh, int32_t R) {
     if (check_joint(sh, R)) return 0;
-    return compress_ws_base(*sh);
+    return compress_ws_base(*sh) + joint_project_ws_bytes(*sh, R);
 }
 
 size_t varrate_joint_decode_workspace_bytes(const varrate_shape* sh, int32_t R, int32_t S, int32_t Q) {
@@ -527,9 +527,10 @@ int varrate_joint_compress(const varrate_shape* sh, const void* K, const void* V
     if (!K || !V || !Qw || !W) return fail(VARRATE_EINVAL, "inputs must be non-NULL");
     if (!aligned16(K) || !aligned16(V) || !aligned16(Qw) || !aligned16(W))
         return fail(VARRATE_EINVAL, "K, V, Qw, W must be 16-byte aligned");
-    if ((rc = ws_check(ws, ws_bytes, compress_ws_base(*sh)))) return rc;
+    if ((rc = ws_check(ws, ws_bytes, varrate_joint_compress_workspace_bytes(sh, c->R)))) return rc;
     hipStream_t st = (hipStream_t)stream;
     uint8_t* w0 = (uint8_t*)ws;
+    uint8_t* wp = w0 + compress_ws_base(*sh);
     float* sbar = sbar_out ? sbar_out
                            : (float*)(w0 + align256(salience_ws_bytes(*sh)) + align256(allocate_ws_bytes(*sh)));
     c->N = sh->n - sh->w;
@@ -537,12 +538,10 @@ int varrate_joint_compress(const varrate_shape* sh, const void* K, const void* V
     if ((rc = hip_status(launch_salience(*sh, K, Qw, sbar, w0, st, false), "salience launch"))) return rc;
     uint8_t* w8 = w0 + align256(salience_ws_bytes(*sh));
     if ((rc = hip_status(launch_allocate_joint(*sh, c->R, c->B, sbar, c->rank, c->offset, c->chunk_off, w8, st,
-                                               salience_part(*sh, w0)),
+                                               salience_part(*sh, w0), joint_lists(*sh, c->R, wp)),
                          "allocate launch")))
         return rc;
-    if ((rc = hip_status(launch_joint_project(*sh, c->R, K, V, W, c->rank, c->offset, c->coef, st), "project launch")))
-        return rc;
-    if ((rc = hip_status(launch_joint_window(*sh, K, V, *c, st), "window copy"))) return rc;
+    if ((rc = hip_status(launch_joint_project(*sh, c->R, K, V, W, *c, wp, st), "project launch"))) return rc;
     c->n_exact = sh->w;
     return VARRATE_OK;
 }

@@ -68,14 +68,23 @@ constexpr size_t ROPE_FRAG_BYTES = (size_t)4 * 8 * 2 * 64 * 16;   // per KV head
 hipError_t launch_rope_prep(const varrate_shape& sh, const float* PK, void* frags, float* freq, hipStream_t st);
 
 // shared cross-head basis
+// bf16 layers: per block of 128 coefficients the tokens that keep any of them, in token order
+// (written by the allocation's last passes for the projection; null for fp32 layers)
+struct JointLists {
+    uint32_t* list;       // [nb][N]
+    uint32_t* list_n;     // [nb]
+    uint4* ccnt;          // [n_chunks] eight 16-bit counts: the chunk's tokens in each list
+    int nb;               // R / 128
+};
+JointLists joint_lists(const varrate_shape& sh, int R, uint8_t* ws);
+size_t joint_project_ws_bytes(const varrate_shape& sh, int R);
 hipError_t launch_allocate_joint(const varrate_shape& sh, int R, int64_t B, const float* sbar, uint16_t* rank,
                                  uint32_t* offset, uint32_t* chunk_off, uint8_t* ws, hipStream_t st,
-                                 const float* s_part);
+                                 const float* s_part, const JointLists& lists);
+// the projection (ws: joint_project_ws_bytes, with the lists filled in) and the window rows
 hipError_t launch_joint_project(const varrate_shape& sh, int R, const void* K, const void* V, const float* W,
-                                const uint16_t* rank, const uint32_t* offset, void* coef, hipStream_t st);
+                                varrate_jcache& c, uint8_t* ws, hipStream_t st);
 size_t joint_decode_ws_bytes(const varrate_shape& sh, int R, int S, int Q);
-hipError_t launch_joint_window(const varrate_shape& sh, const void* K, const void* V, varrate_jcache& c,
-                               hipStream_t st);
 hipError_t launch_joint_decode(const varrate_shape& sh, int R, const varrate_jcache* caches, int S, const void* q,
                                int Q, const float* W, void* out, uint8_t* ws, hipStream_t st);
 

@@ -195,3 +195,32 @@ def test_joint_multi_sequence_appended(vr, oracle_lib, Q):
     say(f"[joint multi Q={Q}] worst decode rel err {worst:.3e}")
     assert caches[0].n_exact == 32 + extra
     assert worst <= DEC_TOL_BF16
+
+
+@pytest.mark.parametrize("N,G,R,kappa,r_min", [
+    (1, 1, 256, 99, 0), (63, 1, 256, 80, 0), (64, 2, 512, 90, 16), (65, 2, 256, 45, 1), (257, 2, 512, 60, 0),
+    (12288, 1, 256, 30, 0), (12289, 2, 512, 20, 0), (12800, 1, 256, 70, 128)])
+def test_joint_projection_tile_edges(vr, N, G, R, kappa, r_min):
+    """The projection over token lists where its tiles and lists end: 64- and 256-token tiles one
+    short of, at and past a multiple, both sides of the switch between them, tokens of rank 0,
+    single coefficients.  Against Z W^T in 64 bits within the bound of the hi + lo basis and one
+    storage rounding; nothing is written past the coded budget."""
+    import torch
+    w = 4
+    shape = vr.Shape(n=N + w, G=G, H=G, w=w, r_min=r_min, kappa_pct=kappa, dtype="bf16")
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    K, V = rnd(N + w, G, 128).bfloat16(), rnd(N + w, G, 128).bfloat16()
+    Qw = (rnd(w, G, 128) * 3).bfloat16()
+    W = torch.linalg.qr(rnd(2 * G * 128, R).cpu()).Q.T.contiguous().cuda()
+    c = vr.joint_compress(shape, K, V, Qw, W)
+    torch.cuda.synchronize()
+    rank, off = c.rank.long(), c.offset.long()
+    assert int(rank.sum()) == c.B and int(rank.min()) >= r_min and int(rank.max()) <= R
+    Z = torch.cat([K[:N].reshape(N, -1), V[:N].reshape(N, -1)], dim=1).double()
+    ref, S = Z @ W.double().T, Z.abs() @ W.double().abs().T
+    keep = torch.arange(R, device="cuda")[None] < rank[:, None]
+    at = (off[:N, None] + torch.arange(R, device="cuda")[None])[keep]
+    got = c.coef.double()
+    assert bool(((got[at] - ref[keep]).abs() <= ref[keep].abs() * 2.0 ** -7 + 2.0 ** -15 * S[keep]).all())
+    assert bool((got[c.B:] == 0).all())
