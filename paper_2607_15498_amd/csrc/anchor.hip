@@ -9,7 +9,7 @@
 //
 //   anc_norms    ||z_a||^2 of every anchor (fp32, fixed summation order)
 //   anc_search   distance GEMM <z_a, z_t> by bf16 MFMA (the bf16 inputs are exact, the fp32
-//                accumulation is the only rounding) on 128-anchor x 128-token tiles; ranking
+//                accumulation is the only rounding) on 128-anchor x 256-token tiles; ranking
 //                key ||z_a||^2 - 2 <z_a, z_t> (||z_t||^2 is common to a token's candidates);
 //                each tile leaves every token's 4 best (key, anchor) pairs
 //   anc_merge    a token's partial lists -> its 4 nearest anchors, nearest first (ties to the
@@ -20,13 +20,13 @@
 //   anc_lists    after the allocation: the anchors of each stored position, per anchor the
 //                stored positions that use it (counts, scan, fill), and those lists cut into
 //                pieces of 64 entries (hub anchors are used by most tokens)
+#include "vr_gemm.h"
 #include "vr_internal.h"
 
 namespace vr {
 
 constexpr int AN_C = 4;                 // nearest anchors per coded token
-constexpr int AN_TT = 128;              // tokens per search tile
-constexpr int AN_TA = 128;              // anchors per search tile
+constexpr int AN_TA = 128;              // anchors per search tile at least (32 CF)
 
 __host__ __device__ inline int64_t anc_token(int64_t i, int delta) { return i + i / (delta - 1) + 1; }
 
@@ -47,189 +47,206 @@ __global__ __launch_bounds__(256) void anc_norms(const uint16_t* __restrict__ K,
     if (lane == 0) nrm[a] = s;
 }
 
-// Running 4 best (smallest key, ties to the smaller anchor number), sorted.
-struct Top4 {
-    float k[AN_C];
-    uint32_t a[AN_C];
-};
-__device__ __forceinline__ bool anc_less(float k1, uint32_t a1, float k2, uint32_t a2) {
-    return k1 < k2 || (k1 == k2 && a1 < a2);
+// The 4 best (smallest key, ties to the smaller anchor number), sorted, as fp64 values whose
+// high words are the fp32 keys and whose low words are the anchor numbers (complemented under
+// a negative key): doubles order by sign, then by the remaining 63 bits, so they order as
+// (key, anchor) pairs do and a compare-exchange is one minimum and one maximum.  An fp32
+// infinity is a finite double there (a NaN key counts as one); the largest pattern used,
+// AN_NONE, stands for no anchor.
+typedef double Top4[AN_C];
+constexpr unsigned long long AN_NONE = 0x7F800000FFFFFFFFull;     // key +inf
+__device__ __forceinline__ double anc_pack(float key, uint32_t a) {
+    const uint32_t k = __float_as_uint(key);
+    const uint32_t lo = a ^ (uint32_t)((int32_t)k >> 31);
+    return __builtin_bit_cast(double, ((unsigned long long)k << 32) | lo);
 }
-__device__ __forceinline__ void top4_init(Top4& t) {
-#pragma unroll
-    for (int j = 0; j < AN_C; ++j) { t.k[j] = INFINITY; t.a[j] = 0xFFFFFFFFu; }
+__device__ __forceinline__ uint32_t anc_number(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    return (uint32_t)b ^ (uint32_t)((int64_t)b >> 63);
 }
-__device__ __forceinline__ void top4_push(Top4& t, float k, uint32_t a) {
-    if (!anc_less(k, a, t.k[AN_C - 1], t.a[AN_C - 1])) return;
-    t.k[AN_C - 1] = k;
-    t.a[AN_C - 1] = a;
+__device__ __forceinline__ double anc_min(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ double anc_max(double a, double b) { return __builtin_fmax(a, b); }
+__device__ __forceinline__ void anc_cx(double& a, double& b) {
+    const double t = anc_min(a, b);
+    b = anc_max(a, b);
+    a = t;
+}
+__device__ __forceinline__ void top4_sort(Top4& t) {
+    anc_cx(t[0], t[1]);
+    anc_cx(t[2], t[3]);
+    anc_cx(t[0], t[2]);
+    anc_cx(t[1], t[3]);
+    anc_cx(t[1], t[2]);
+}
+// t = the 4 smallest of two sorted lists, sorted (a bitonic half-cleaner, then its merge)
+__device__ __forceinline__ void top4_merge(Top4& t, const Top4& o) {
 #pragma unroll
-    for (int j = AN_C - 1; j > 0; --j) {
-        if (anc_less(t.k[j], t.a[j], t.k[j - 1], t.a[j - 1])) {
-            const float tk = t.k[j]; t.k[j] = t.k[j - 1]; t.k[j - 1] = tk;
-            const uint32_t ta = t.a[j]; t.a[j] = t.a[j - 1]; t.a[j - 1] = ta;
+    for (int q = 0; q < AN_C; ++q) t[q] = anc_min(t[q], o[AN_C - 1 - q]);
+    anc_cx(t[0], t[2]);
+    anc_cx(t[1], t[3]);
+    anc_cx(t[0], t[1]);
+    anc_cx(t[2], t[3]);
+}
+// merged with the list of lane ^ 16 (SWAP 16) or lane ^ 32
+template <int SWAP> __device__ __forceinline__ void top4_lanes(Top4& t) {
+    Top4 o;
+    const bool upper = (threadIdx.x & SWAP) != 0;
+#pragma unroll
+    for (int q = 0; q < AN_C; ++q) {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, t[q]);
+        uint32_t w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t x = (uint32_t)(b >> (32 * h));
+            // of the two results one is the lane's own value and the other its partner's
+            if constexpr (SWAP == 16) {
+                const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+                w[h] = upper ? r[0] : r[1];
+            } else {
+                const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+                w[h] = upper ? r[0] : r[1];
+            }
         }
+        o[q] = __builtin_bit_cast(double, ((unsigned long long)w[1] << 32) | w[0]);
     }
+    top4_merge(t, o);
 }
 
-// ---- distance GEMM + per-tile top 4.  Workgroup: 4 waves, 128 anchors x 128 tokens; wave
-// (wa, wt) = (wave / 2, wave % 2) computes anchors 64 wa .. 64 wa + 63 (four 16-row tiles, A
-// operand) against tokens 64 wt .. 64 wt + 63 (four 16-column tiles, B operand): 16 MFMA
-// 16x16x32 per step of 32 elements of z.  Both operands are staged in LDS in fragment order by
-// direct-to-LDS loads: one 1 KB load per 16-row (or 16-column) tile and step, lane l bringing
-// row l % 16's elements 8 (l / 16) .. + 7, so every fragment read is one conflict-free 16-byte
-// read per lane.  AS_NS stages of 16 KB rotate (each wave issues 4 loads per stage and waits
-// on its own load count); a step's barrier also frees the buffer the next issue reuses.  Three
-// stages measured best: 0.53 ms for the 32K layer against 0.61 with four and 0.82 with eight
-// (one workgroup per CU then), and 0.65 ms for the earlier form (one step of lookahead, the
-// token operand loaded straight into registers).
-// C[anchor][token]: lane -> token column (lane % 16) and anchors 4 (lane / 16) + v of each
-// 16-anchor row tile.  Workgroups are mapped so that all anchor tiles of one token tile run on
-// the same XCD (its token rows stay in that XCD's L2).
-constexpr int AS_NS = 3;                                 // stages in the ring (three workgroups per CU)
-constexpr int AS_STAGE = (AN_TA / 16 + AN_TT / 16) * 1024;   // bytes per stage (A then B tiles)
-constexpr size_t AS_LDS = (size_t)AS_NS * AS_STAGE;      // 48 KB
-static_assert(AN_TA == 128 && AN_TT == 128, "one 1 KB load per 16-row tile; 16 loads per stage");
-
+// ---- distance products and each anchor tile's 4 best per token: a workgroup per (64 TF tokens,
+// 32 CF anchors), gemm_tile with the anchors as columns.  C[anchor][token]: lane -> token
+// column (lane % 16) and anchors 4 (lane / 16) + v of each 16-anchor tile, so a lane sorts 16
+// keys per token in registers, the four lanes of a token merge by lane swaps, the two anchor
+// halves through LDS.  Workgroups are mapped so that all anchor tiles of one token tile run on
+// the same XCD (its token rows stay in that XCD's L2).  Matrix-core bound; 32768-token Llama
+// layer (2046 anchors, 257 GFLOP): 508 us with 64 x 64 wave tiles and lists kept by insertion,
+// 250 us now (1030 TFLOP/s).
 struct AnSearch {
     const uint16_t* K;
     const uint16_t* V;
     const float* nrm;
-    float* pk;          // [n_atiles][Nc][4] partial keys
-    uint32_t* pa;       // [n_atiles][Nc][4] partial anchor numbers
+    double* part;       // [n_atiles][Nc][4] packed partial lists
     int64_t Nc, na;
     int delta, GD, n_ttiles, n_atiles;
 };
 
-__device__ __forceinline__ const uint16_t* anc_zrow(const AnSearch& p, int64_t t, int k) {
-    // element k (a multiple of 8) of z_t
-    return k < p.GD ? p.K + t * p.GD + k : p.V + t * p.GD + (k - p.GD);
-}
-
-__global__ __launch_bounds__(256) void anc_search(AnSearch p) {
+template <int TF, int CF>
+__global__ __launch_bounds__(512, 2) void anc_search(AnSearch p) {
+    typedef GemmTile<TF, CF, false> T;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int col = lane & 15, grp = lane >> 4;
-    const int wa = wave >> 1, wt = wave & 1;
-    // XCD-aware order: the 8 XCDs take consecutive workgroup ids in turn
-    const int b = blockIdx.x;
-    const int xcd = b & 7, k = b >> 3;
-    const int tt = xcd + 8 * (k / p.n_atiles), at = k % p.n_atiles;
-    if (tt >= p.n_ttiles) return;
-    const int64_t i0 = (int64_t)tt * AN_TT;
-    const int64_t a0 = (int64_t)at * AN_TA;
-    // this wave's loads of a stage: A row tiles 2 wave, 2 wave + 1 and B column tiles 2 wave,
-    // 2 wave + 1; lane row l % 16, elements 8 (l / 16) .. + 7 of the step (rows clamped: rows
-    // past the anchors or tokens are dropped later)
-    int64_t lrow[4];
+    const int wa = wave >> 2, wt = wave & 3;
+    // XCD x (workgroup id mod 8) takes the x-th eighth of the anchor-tile-major order
+    const int per = (p.n_ttiles * p.n_atiles + 7) / 8, id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    const int at = id / p.n_ttiles, tt = id % p.n_ttiles;
+    if (at >= p.n_atiles) return;
+    const int64_t i0 = (int64_t)tt * T::TOK;
+    const int64_t a0 = (int64_t)at * T::ROWS;
+    // rows past the anchors or tokens are clamped here and dropped later
+    const uint8_t* tok[T::TL];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        int64_t a = a0 + 16 * (2 * wave + u) + col;
-        a = a < p.na ? a : p.na - 1;
-        lrow[u] = a * p.delta;
-        int64_t i = i0 + 16 * (2 * wave + u) + col;
+    for (int u = 0; u < T::TL; ++u) {
+        int64_t i = i0 + gemm_row(T::TL * wave + u);
         i = i < p.Nc ? i : p.Nc - 1;
-        lrow[2 + u] = anc_token(i, p.delta);
+        tok[u] = reinterpret_cast<const uint8_t*>(p.K + anc_token(i, p.delta) * p.GD + 8 * gemm_piece());
     }
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem);
-    const int steps = 2 * p.GD / 32;
-    auto issue = [&](int s) {
-        const int kk = 32 * s + 8 * grp;
-        const uint32_t st = lds0 + (uint32_t)(s % AS_NS) * AS_STAGE;
+    const uint8_t* anc[T::CL];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            // tile index in the stage: A tiles 0..7, then B tiles 8..15
-            const uint32_t dst = st + 1024u * (uint32_t)((u < 2 ? 0 : 8) + 2 * wave + (u & 1));
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                         :: "v"(anc_zrow(p, lrow[u], kk)), "s"(dst) : "memory", "m0");
+    for (int u = 0; u < T::CL; ++u) {
+        int64_t a = a0 + gemm_row(T::CL * wave + u);
+        a = a < p.na ? a : p.na - 1;
+        anc[u] = reinterpret_cast<const uint8_t*>(p.K + a * p.delta * p.GD + 8 * gemm_piece());
+    }
+    const int64_t jump = reinterpret_cast<const uint8_t*>(p.V) - reinterpret_cast<const uint8_t*>(p.K) - 2 * (int64_t)p.GD;
+    const int steps = 2 * p.GD / 64;
+    f32x4 acc[CF][TF];                        // [anchor tile][token tile] of this wave
+    gemm_tile<TF, CF, false>(smem, tok, anc, jump, steps, acc);
+    // the lane's anchors and their norms (absent anchors, numbers na and up: +inf keys, behind
+    // every real anchor's, of which there are at least four)
+    float nrm[CF][4];
+#pragma unroll
+    for (int j = 0; j < CF; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t a = a0 + 16 * (CF * wa + j) + 4 * grp + v;
+            nrm[j][v] = a < p.na ? p.nrm[a] : INFINITY;
         }
-    };
-    f32x4 acc[4][4];                          // [row tile][column tile] of this wave
+    double* xt = reinterpret_cast<double*>(smem);              // [wt][TF token tiles][16][4]
+    const uint32_t an = (uint32_t)(a0 + 16 * CF * wa + 4 * grp);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[j][c] = f32x4{0, 0, 0, 0};
-    for (int s = 0; s < AS_NS - 1 && s < steps; ++s) issue(s);
-    for (int s = 0; s < steps; ++s) {
-        // stage s has landed when at most the loads of the stages after it are in flight
-        static_assert(AS_NS == 3, "the wait below leaves one later stage (4 loads) in flight");
-        if (s + AS_NS - 2 < steps) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();                      // every wave's part of stage s; stage s - 1 is free
-        if (s + AS_NS - 1 < steps) issue(s + AS_NS - 1);
-        const u32x4* sa = reinterpret_cast<const u32x4*>(smem + (size_t)(s % AS_NS) * AS_STAGE);
-        const u32x4* sb = sa + 8 * 64;
-        u32x4 fa[4], fb[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) fa[j] = sa[(4 * wa + j) * 64 + lane];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) fb[c] = sb[(4 * wt + c) * 64 + lane];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[j][c] = mfma(fa[j], fb[c], acc[j][c]);
-    }
-    // ---- keys and the 4 best per token of this wave's 64 anchors: per lane, then over the 4
-    //      lanes of a token; then the two anchor halves of the workgroup through LDS
-    __syncthreads();                          // every wave is done with the stages
-    float* xk = reinterpret_cast<float*>(smem);                  // [wt][4 col tiles][16][4]
-    uint32_t* xa = reinterpret_cast<uint32_t*>(smem + 2 * 4 * 16 * AN_C * 4);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < TF; ++c) {
         Top4 t;
-        top4_init(t);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < CF; ++j) {
+            Top4 o;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int64_t a = a0 + 64 * wa + 16 * j + 4 * grp + v;
-                if (a < p.na) top4_push(t, p.nrm[a] - 2.f * acc[j][c][v], (uint32_t)a);
+                const uint32_t a = an + 16 * j + v;
+                o[v] = anc_pack(fminf(nrm[j][v] - 2.f * acc[j][c][v], INFINITY), a);
             }
+            top4_sort(o);
+            if (j == 0) {
 #pragma unroll
-        for (int m = 16; m <= 32; m <<= 1) {
-            float ok[AN_C];
-            uint32_t oa[AN_C];
-#pragma unroll
-            for (int q = 0; q < AN_C; ++q) {
-                ok[q] = __shfl_xor(t.k[q], m, 64);
-                oa[q] = (uint32_t)__shfl_xor((int)t.a[q], m, 64);
-            }
-#pragma unroll
-            for (int q = 0; q < AN_C; ++q) top4_push(t, ok[q], oa[q]);
-        }
-        const int slot = ((wt * 4 + c) * 16 + col) * AN_C;
-        if (wa == 1 && grp == 0) {
-#pragma unroll
-            for (int q = 0; q < AN_C; ++q) { xk[slot + q] = t.k[q]; xa[slot + q] = t.a[q]; }
-        }
-        __syncthreads();
-        if (wa == 0) {
-#pragma unroll
-            for (int q = 0; q < AN_C; ++q) top4_push(t, xk[slot + q], xa[slot + q]);
-            const int64_t i = i0 + 64 * wt + 16 * c + col;
-            if (grp == 0 && i < p.Nc) {
-                const int64_t o = ((int64_t)at * p.Nc + i) * AN_C;
-#pragma unroll
-                for (int q = 0; q < AN_C; ++q) { p.pk[o + q] = t.k[q]; p.pa[o + q] = t.a[q]; }
+                for (int q = 0; q < AN_C; ++q) t[q] = o[q];
+            } else {
+                top4_merge(t, o);
             }
         }
+        top4_lanes<16>(t);
+        top4_lanes<32>(t);
+        // lane group g of the token's four holds entry g
+        const double mine = grp == 0 ? t[0] : grp == 1 ? t[1] : grp == 2 ? t[2] : t[3];
+        if (wa == 1) {
+            xt[((wt * TF + c) * 16 + col) * AN_C + grp] = mine;
+        } else {
+            acc[0][c] = __builtin_bit_cast(f32x4, (double2){t[0], t[1]});
+            acc[1][c] = __builtin_bit_cast(f32x4, (double2){t[2], t[3]});
+        }
+    }
+    __syncthreads();
+    if (wa == 1) return;
+#pragma unroll
+    for (int c = 0; c < TF; ++c) {
+        const double2 lo = __builtin_bit_cast(double2, acc[0][c]), hi = __builtin_bit_cast(double2, acc[1][c]);
+        Top4 t = {lo.x, lo.y, hi.x, hi.y}, o;
+        const int slot = ((wt * TF + c) * 16 + col) * AN_C;
+#pragma unroll
+        for (int q = 0; q < AN_C; ++q) o[q] = xt[slot + q];
+        top4_merge(t, o);
+        const int64_t i = i0 + 16 * (TF * wt + c) + col;
+        const double mine = grp == 0 ? t[0] : grp == 1 ? t[1] : grp == 2 ? t[2] : t[3];
+        if (i < p.Nc) p.part[((int64_t)at * p.Nc + i) * AN_C + grp] = mine;
     }
 }
 
-// ---- merge of the partial lists: one thread per coded token
-__global__ __launch_bounds__(256) void anc_merge(const float* __restrict__ pk, const uint32_t* __restrict__ pa,
-                                                int64_t Nc, int n_atiles, uint16_t* __restrict__ nn) {
+// ---- merge of the partial lists: one thread per coded token, all of a batch's loads in flight
+__global__ __launch_bounds__(256) void anc_merge(const double* __restrict__ part, int64_t Nc, int n_atiles,
+                                                uint16_t* __restrict__ nn) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= Nc) return;
     Top4 t;
-    top4_init(t);
-    for (int at = 0; at < n_atiles; ++at) {
-        const int64_t o = ((int64_t)at * Nc + i) * AN_C;
 #pragma unroll
-        for (int q = 0; q < AN_C; ++q) top4_push(t, pk[o + q], pa[o + q]);
+    for (int q = 0; q < AN_C; ++q) t[q] = __builtin_bit_cast(double, AN_NONE);
+    for (int at = 0; at < n_atiles; at += 4) {
+        u32x4 w[4][2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double* src = part + ((int64_t)(at + k < n_atiles ? at + k : at) * Nc + i) * AN_C;
+            w[k][0] = load16(src);
+            w[k][1] = load16(src + 2);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (at + k >= n_atiles) break;
+            const double2 lo = __builtin_bit_cast(double2, w[k][0]), hi = __builtin_bit_cast(double2, w[k][1]);
+            const Top4 o = {lo.x, lo.y, hi.x, hi.y};
+            top4_merge(t, o);
+        }
     }
-#pragma unroll
-    for (int q = 0; q < AN_C; ++q) nn[i * AN_C + q] = (uint16_t)t.a[q];
+    uint2 out;
+    out.x = pack2(anc_number(t[0]) & 0xFFFFu, anc_number(t[1]) & 0xFFFFu);
+    out.y = pack2(anc_number(t[2]) & 0xFFFFu, anc_number(t[3]) & 0xFFFFu);
+    *reinterpret_cast<uint2*>(nn + i * AN_C) = out;
 }
 
 // ---- compaction, residuals and the anchor store.  One wave per (row, head) piece of 128
@@ -351,7 +368,7 @@ size_t anchor_ws_bytes(const varrate_shape& sh) {
     const int64_t Np = sh.n - sh.w, Nc = coded_count(sh), na = anchor_count(sh);
     const size_t rows = (size_t)(Nc + sh.w) * sh.G * D * 2;
     return align256(salience_ws_bytes(sh)) + align256(allocate_ws_bytes(sh)) + align256((size_t)Np * 4) +
-           align256((size_t)Nc * 4) + align256((size_t)na * 4) + 2 * align256((size_t)anc_atiles(sh) * Nc * AN_C * 4) +
+           align256((size_t)Nc * 4) + align256((size_t)na * 4) + align256((size_t)anc_atiles(sh) * Nc * AN_C * 8) +
            align256((size_t)Nc * AN_C * 2) + 2 * align256(rows) + align256((size_t)na * 4);
 }
 
@@ -365,13 +382,26 @@ AnchorWs anchor_ws(const varrate_shape& sh, uint8_t* ws) {
     w.sbar = (float*)p;       p += align256((size_t)Np * 4);
     w.sbar_c = (float*)p;     p += align256((size_t)Nc * 4);
     w.nrm = (float*)p;        p += align256((size_t)na * 4);
-    w.pk = (float*)p;         p += align256((size_t)anc_atiles(sh) * Nc * AN_C * 4);
-    w.pa = (uint32_t*)p;      p += align256((size_t)anc_atiles(sh) * Nc * AN_C * 4);
+    w.part = (double*)p;      p += align256((size_t)anc_atiles(sh) * Nc * AN_C * 8);
     w.nn = (uint16_t*)p;      p += align256((size_t)Nc * AN_C * 2);
     w.Kr = p;                 p += align256(rows);
     w.Vr = p;                 p += align256(rows);
     w.cnt = (uint32_t*)p;
     return w;
+}
+
+template <int TF, int CF>
+static hipError_t launch_search(AnSearch& p, hipStream_t st) {
+    typedef GemmTile<TF, CF, false> T;
+    static_assert(T::LDS >= 4 * TF * 16 * AN_C * 8, "the halves' lists fit the stages");
+    static_assert(T::ROWS >= AN_TA, "the workspace holds every tile's lists");
+    p.n_atiles = (int)((p.na + T::ROWS - 1) / T::ROWS);
+    p.n_ttiles = (int)((p.Nc + T::TOK - 1) / T::TOK);
+    const int64_t per_xcd = ((int64_t)p.n_ttiles * p.n_atiles + 7) / 8;
+    const hipError_t e = ensure_lds_limit((const void*)anc_search<TF, CF>, T::LDS);
+    if (e != hipSuccess) return e;
+    anc_search<TF, CF><<<(unsigned)(8 * per_xcd), 512, T::LDS, st>>>(p);
+    return hipGetLastError();
 }
 
 hipError_t launch_anchor_search(const varrate_shape& sh, const void* K, const void* V, uint16_t* nn,
@@ -384,20 +414,17 @@ hipError_t launch_anchor_search(const varrate_shape& sh, const void* K, const vo
     p.K = (const uint16_t*)K;
     p.V = (const uint16_t*)V;
     p.nrm = w.nrm;
-    p.pk = w.pk;
-    p.pa = w.pa;
+    p.part = w.part;
     p.Nc = Nc;
     p.na = na;
     p.delta = sh.anchor_stride;
     p.GD = GD;
-    p.n_ttiles = (int)((Nc + AN_TT - 1) / AN_TT);
-    p.n_atiles = anc_atiles(sh);
-    // 8 XCDs, each with ceil(n_ttiles / 8) token tiles x n_atiles anchor tiles
-    const int64_t per_xcd = (int64_t)((p.n_ttiles + 7) / 8) * p.n_atiles;
-    hipError_t e = ensure_lds_limit((const void*)anc_search, AS_LDS);
+    // 256 x 256 tiles do the most per LDS byte; 64 tokens x 128 anchors where those would leave
+    // CUs idle
+    const bool wide = (Nc + 255) / 256 * ((na + 255) / 256) >= 192;
+    hipError_t e = wide ? launch_search<4, 8>(p, st) : launch_search<1, 4>(p, st);
     if (e != hipSuccess) return e;
-    anc_search<<<(unsigned)(8 * per_xcd), 256, AS_LDS, st>>>(p);
-    anc_merge<<<(unsigned)((Nc + 255) / 256), 256, 0, st>>>(w.pk, w.pa, Nc, p.n_atiles, nn);
+    anc_merge<<<(unsigned)((Nc + 255) / 256), 256, 0, st>>>(w.part, Nc, p.n_atiles, nn);
     return hipGetLastError();
 }
 

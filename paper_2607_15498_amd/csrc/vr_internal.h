@@ -41,8 +41,7 @@ struct AnchorWs {
     float* sbar;          // [n - w] pooled salience of the whole prefix
     float* sbar_c;        // [N] coded tokens' salience
     float* nrm;           // [na]
-    float* pk;            // [n_atiles][N][4]
-    uint32_t* pa;         // [n_atiles][N][4]
+    double* part;         // [n_atiles][N][4] packed (key, anchor) lists of the search
     uint16_t* nn;         // [N][4]
     void* Kr;             // [N + w][G][d] residuals, then the window rows
     void* Vr;
