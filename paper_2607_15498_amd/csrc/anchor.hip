@@ -17,9 +17,9 @@
 //   anc_prep     coded salience gathered from the prefix's, residuals k_t - mean, v_t - mean
 //                (fp32, stored in the layer's dtype) followed by the window rows, and the
 //                anchor rows copied to their store
-//   anc_lists    after the allocation: the anchors of each stored position, per anchor the
-//                stored positions that use it (counts, scan, fill), and those lists cut into
-//                pieces of 64 entries (hub anchors are used by most tokens)
+//   anc_count, anc_lists, anc_fill  after the allocation: the anchors of each stored position,
+//                per anchor the stored positions that use it (counts, scan, fill), and those
+//                lists cut into pieces of 64 entries (hub anchors are used by most tokens)
 #include "vr_gemm.h"
 #include "vr_internal.h"
 
@@ -30,17 +30,37 @@ constexpr int AN_TA = 128;              // anchors per search tile at least (32 
 
 __host__ __device__ inline int64_t anc_token(int64_t i, int delta) { return i + i / (delta - 1) + 1; }
 
-// ---- anchor norms: one wave per anchor
+// ---- anchor norms: one wave per anchor, its row staged in LDS by 16-byte loads and summed
+// with lane l taking elements l, l + 64, .. in order (latency bound: 14 us for 2046 anchors of
+// 2048 elements with 2-byte loads, 4.8 with these)
+constexpr int AN_NP = 2048;             // elements staged at a time
 __global__ __launch_bounds__(256) void anc_norms(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                                                 int64_t na, int delta, int GD, float* __restrict__ nrm) {
-    const int64_t a = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (a >= na) return;
+    __shared__ __attribute__((aligned(16))) uint16_t row[4][AN_NP];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t a = (int64_t)blockIdx.x * 4 + wave;
+    if (a >= na) return;                // (no workgroup barrier below)
     const int64_t t = a * delta;
     float s = 0.f;
-    for (int k = lane; k < 2 * GD; k += 64) {
-        const float x = bf16_to_f32(k < GD ? K[t * GD + k] : V[t * GD + k - GD]);
-        s = fmaf(x, x, s);
+    for (int k0 = 0; k0 < 2 * GD; k0 += AN_NP) {
+        const int n = 2 * GD - k0 < AN_NP ? 2 * GD - k0 : AN_NP;        // a multiple of 256
+        u32x4 w[AN_NP / 512];
+#pragma unroll
+        for (int u = 0; u < AN_NP / 512; ++u) {
+            const int e = 512 * u + 8 * lane, k = k0 + (e < n ? e : 0);
+            w[u] = load16(k < GD ? K + t * GD + k : V + t * GD + k - GD);
+        }
+#pragma unroll
+        for (int u = 0; u < AN_NP / 512; ++u) *reinterpret_cast<u32x4*>(&row[wave][512 * u + 8 * lane]) = w[u];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 8
+        for (int k = lane; k < n; k += 64) {
+            const float x = bf16_to_f32(row[wave][k]);
+            s = fmaf(x, x, s);
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -249,116 +269,197 @@ __global__ __launch_bounds__(256) void anc_merge(const double* __restrict__ part
     *reinterpret_cast<uint2*>(nn + i * AN_C) = out;
 }
 
-// ---- compaction, residuals and the anchor store.  One wave per (row, head) piece of 128
-// elements; rows: coded tokens i < Nc (residual), window rows (copied), anchors (copied).
-template <typename ET>
-__global__ __launch_bounds__(256) void anc_prep(const ET* __restrict__ K, const ET* __restrict__ V,
+// ---- compaction, residuals and the anchor store.  A workgroup per (64 rows, head), 16 lanes
+// per 256-byte row piece and 8 elements per lane; rows: coded tokens i < Nc (residual), window
+// rows (copied), anchors (copied).  Consecutive workgroups take consecutive heads, so with 8 (or
+// 4) heads one XCD gathers the anchors of one head (512 KB at 2046 anchors) from its L2.  Bound
+// by the K and V it reads and the residuals it writes: 118 us for the 32768-token Llama layer
+// with 2-byte accesses and all heads on every XCD, 55 us now.  It also clears the list counts.
+constexpr int AP_ROWS = 64;
+__global__ __launch_bounds__(256) void anc_prep(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                                                const float* __restrict__ sbar, const uint16_t* __restrict__ nn,
                                                int64_t N, int64_t Nc, int64_t na, int w, int G, int delta,
-                                               float* __restrict__ sbar_c, ET* __restrict__ Kr, ET* __restrict__ Vr,
-                                               ET* __restrict__ Ka, ET* __restrict__ Va) {
-    const int64_t piece = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t rows = Nc + w + na;
-    if (piece >= rows * G) return;
-    const int64_t r = piece / G;
-    const int g = (int)(piece % G);
+                                               float* __restrict__ sbar_c, uint16_t* __restrict__ Kr,
+                                               uint16_t* __restrict__ Vr, uint16_t* __restrict__ Ka,
+                                               uint16_t* __restrict__ Va, uint32_t* __restrict__ cnt) {
+    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (gid < na) cnt[gid] = 0u;
+    const int g = blockIdx.x % G;
+    const int64_t r0 = (int64_t)(blockIdx.x / G) * AP_ROWS + (threadIdx.x >> 4);
+    const int e = g * D + 8 * (threadIdx.x & 15);
     const int GD = G * D;
-    for (int e = lane; e < D; e += 64) {
+    const int64_t rows = Nc + w + na;
+    uint2 near[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t r = r0 + 16 * k;
+        near[k] = *reinterpret_cast<const uint2*>(nn + (r < Nc ? r : 0) * AN_C);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t r = r0 + 16 * k;
         if (r < Nc) {
             const int64_t t = anc_token(r, delta);
-            float mk = 0.f, mv = 0.f;
+            const int64_t ta[AN_C] = {(int64_t)(near[k].x & 0xFFFFu) * delta, (int64_t)(near[k].x >> 16) * delta,
+                                      (int64_t)(near[k].y & 0xFFFFu) * delta, (int64_t)(near[k].y >> 16) * delta};
+            u32x4 x[2], m[2][AN_C];
+            x[0] = load16(K + t * GD + e);
+            x[1] = load16(V + t * GD + e);
 #pragma unroll
-            for (int q = 0; q < AN_C; ++q) {            // fixed order: nearest first
-                const int64_t ta = (int64_t)nn[r * AN_C + q] * delta;
-                mk += elem_f(K[ta * GD + g * D + e]);
-                mv += elem_f(V[ta * GD + g * D + e]);
+            for (int q = 0; q < AN_C; ++q) {
+                m[0][q] = load16(K + ta[q] * GD + e);
+                m[1][q] = load16(V + ta[q] * GD + e);
             }
-            mk *= 1.f / AN_C;
-            mv *= 1.f / AN_C;
-            Kr[r * GD + g * D + e] = to_elem<ET>(elem_f(K[t * GD + g * D + e]) - mk);
-            Vr[r * GD + g * D + e] = to_elem<ET>(elem_f(V[t * GD + g * D + e]) - mv);
-            if (g == 0 && e == 0) sbar_c[r] = sbar[t];
-        } else if (r < Nc + w) {
-            const int64_t t = N + (r - Nc);
-            Kr[r * GD + g * D + e] = K[t * GD + g * D + e];
-            Vr[r * GD + g * D + e] = V[t * GD + g * D + e];
-        } else {
-            const int64_t a = r - Nc - w;
-            Ka[a * GD + g * D + e] = K[a * delta * GD + g * D + e];
-            Va[a * GD + g * D + e] = V[a * delta * GD + g * D + e];
+#pragma unroll
+            for (int kv = 0; kv < 2; ++kv) {
+                u32x4 o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float lo = 0.f, hi = 0.f;                    // fixed order: nearest first
+#pragma unroll
+                    for (int q = 0; q < AN_C; ++q) {
+                        lo += bf_lo(m[kv][q][i]);
+                        hi += bf_hi(m[kv][q][i]);
+                    }
+                    o[i] = cvt_bf16x2(bf_lo(x[kv][i]) - lo * (1.f / AN_C), bf_hi(x[kv][i]) - hi * (1.f / AN_C));
+                }
+                *reinterpret_cast<u32x4*>((kv ? Vr : Kr) + r * GD + e) = o;
+            }
+            if (e == 0) sbar_c[r] = sbar[t];
+        } else if (r < rows) {
+            const bool win = r < Nc + w;
+            const int64_t a = r - Nc - w, t = win ? N + (r - Nc) : a * delta;
+            const u32x4 xk = load16(K + t * GD + e), xv = load16(V + t * GD + e);
+            *reinterpret_cast<u32x4*>((win ? Kr + r * GD : Ka + a * GD) + e) = xk;
+            *reinterpret_cast<u32x4*>((win ? Vr + r * GD : Va + a * GD) + e) = xv;
         }
     }
 }
 
-// ---- after the allocation: anchors of every stored position, and the inverse lists
-__global__ __launch_bounds__(256) void anc_count(const uint32_t* __restrict__ sidx, const uint16_t* __restrict__ nn,
-                                                int64_t Nc, uint16_t* __restrict__ snn, uint32_t* __restrict__ cnt) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= Nc) return;
-    const int64_t i = sidx[p];
-#pragma unroll
-    for (int q = 0; q < AN_C; ++q) {
-        const uint16_t a = nn[i * AN_C + q];
-        snn[p * AN_C + q] = a;
-        atomicAdd(&cnt[a], 1u);
-    }
-}
+// ---- after the allocation: anchors of every stored position, and the inverse lists.  Hub
+// anchors are among the nearest of a large share of the tokens, so their counts and cursors are
+// kept per workgroup of 1024 tokens in LDS and meet in memory once per workgroup and anchor
+// (atomics of every token on them took 27 and 28 us for 30K tokens; 4.7 and 6.6 now).
+// Past AL_LDS anchors the counts do not fit LDS and lists are short: one atomic per entry.
+constexpr int AL_T = 1024;
+constexpr int64_t AL_LDS = 12288;
 
-// exclusive scan of na counts (one workgroup); the counts become fill cursors (set to the
-// list starts)
-__global__ __launch_bounds__(1024) void anc_scan(uint32_t* __restrict__ cnt, int64_t na, uint32_t* __restrict__ off) {
-    __shared__ uint32_t part[1024];
+template <bool LDS>
+__global__ __launch_bounds__(AL_T) void anc_count(const uint32_t* __restrict__ sidx, const uint16_t* __restrict__ nn,
+                                                 int64_t Nc, int64_t na, uint16_t* __restrict__ snn,
+                                                 uint32_t* __restrict__ cnt) {
+    extern __shared__ uint32_t hist[];
     const int tid = threadIdx.x;
-    const int64_t per = (na + 1023) / 1024;
-    const int64_t b0 = tid * per;
-    uint32_t s = 0;
-    for (int64_t a = b0; a < b0 + per && a < na; ++a) s += cnt[a];
-    part[tid] = s;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const uint32_t v = tid >= o ? part[tid - o] : 0u;
-        __syncthreads();
-        part[tid] += v;
+    const int64_t p = (int64_t)blockIdx.x * AL_T + tid;
+    const int64_t i = sidx[p < Nc ? p : Nc - 1];
+    if constexpr (LDS) {
+        for (int64_t a = tid; a < na; a += AL_T) hist[a] = 0u;
         __syncthreads();
     }
-    uint32_t run = tid ? part[tid - 1] : 0u;
-    for (int64_t a = b0; a < b0 + per && a < na; ++a) {
-        const uint32_t c = cnt[a];
-        off[a] = run;
-        cnt[a] = run;
-        run += c;
+    if (p < Nc) {
+        const uint2 q = *reinterpret_cast<const uint2*>(nn + i * AN_C);
+        *reinterpret_cast<uint2*>(snn + p * AN_C) = q;
+        uint32_t* dst = LDS ? hist : cnt;
+        atomicAdd(&dst[q.x & 0xFFFFu], 1u);
+        atomicAdd(&dst[q.x >> 16], 1u);
+        atomicAdd(&dst[q.y & 0xFFFFu], 1u);
+        atomicAdd(&dst[q.y >> 16], 1u);
     }
-    if (tid == 1023) off[na] = part[1023];
+    if constexpr (LDS) {
+        __syncthreads();
+        for (int64_t a = tid; a < na; a += AL_T)
+            if (hist[a]) atomicAdd(&cnt[a], hist[a]);
+    }
 }
 
-__global__ __launch_bounds__(256) void anc_fill(const uint16_t* __restrict__ snn, int64_t Nc,
-                                               uint32_t* __restrict__ cur, uint32_t* __restrict__ inv) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= Nc) return;
+template <bool LDS>
+__global__ __launch_bounds__(AL_T) void anc_fill(const uint16_t* __restrict__ snn, int64_t Nc, int64_t na,
+                                                uint32_t* __restrict__ cur, uint32_t* __restrict__ inv) {
+    extern __shared__ uint32_t hist[];
+    const int tid = threadIdx.x;
+    const int64_t p = (int64_t)blockIdx.x * AL_T + tid;
+    const bool in = p < Nc;
+    const uint2 q = *reinterpret_cast<const uint2*>(snn + (in ? p : 0) * AN_C);
+    const uint32_t a4[AN_C] = {q.x & 0xFFFFu, q.x >> 16, q.y & 0xFFFFu, q.y >> 16};
+    if constexpr (LDS) {
+        uint32_t slot[AN_C];
+        for (int64_t a = tid; a < na; a += AL_T) hist[a] = 0u;
+        __syncthreads();
+        if (in)
 #pragma unroll
-    for (int q = 0; q < AN_C; ++q) {
-        const uint32_t slot = atomicAdd(&cur[snn[p * AN_C + q]], 1u);
-        inv[slot] = (uint32_t)p;
+            for (int k = 0; k < AN_C; ++k) slot[k] = atomicAdd(&hist[a4[k]], 1u);
+        __syncthreads();
+        // the workgroup's place in each list it adds to
+        for (int64_t a = tid; a < na; a += AL_T)
+            if (hist[a]) hist[a] = atomicAdd(&cur[a], hist[a]);
+        __syncthreads();
+        if (in)
+#pragma unroll
+            for (int k = 0; k < AN_C; ++k) inv[hist[a4[k]] + slot[k]] = (uint32_t)p;
+    } else if (in) {
+#pragma unroll
+        for (int k = 0; k < AN_C; ++k) inv[atomicAdd(&cur[a4[k]], 1u)] = (uint32_t)p;
     }
 }
 
-// pieces of 64 entries per anchor list (hub anchors, used by a large share of the tokens,
-// have long lists): counts, then (after a scan into piece_off) each piece's anchor
-__global__ __launch_bounds__(256) void anc_pcount(const uint32_t* __restrict__ off, int64_t na, uint32_t* __restrict__ cnt) {
-    const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (a < na) cnt[a] = (off[a + 1] - off[a] + 63) / 64;
-}
-__global__ __launch_bounds__(256) void anc_pfill(const uint32_t* __restrict__ poff, int64_t na,
-                                                uint16_t* __restrict__ panchor) {
-    const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (a >= na) return;
-    for (uint32_t k = poff[a]; k < poff[a + 1]; ++k) panchor[k] = (uint16_t)a;
-}
-
-__global__ void anc_zero(uint32_t* __restrict__ x, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = 0u;
+// One workgroup between the two: the exclusive scan of the counts into the list starts (the
+// counts become fill cursors, set to the starts), and the lists cut into pieces of 64 entries
+// (hub anchors have long lists): the scan of the pieces, and each piece's anchor.  A thread takes
+// consecutive anchors; anchors of more than 4 pieces are filled by their whole wave.
+__global__ __launch_bounds__(AL_T) void anc_lists(uint32_t* __restrict__ cnt, int64_t na, uint32_t* __restrict__ off,
+                                                 uint32_t* __restrict__ poff, uint16_t* __restrict__ panchor) {
+    __shared__ uint2 wsum[AL_T / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t per = (na + AL_T - 1) / AL_T;
+    const int64_t b0 = tid * per, b1 = b0 + per < na ? b0 + per : na;
+    uint32_t s = 0, ps = 0;
+    for (int64_t a = b0; a < b1; ++a) {
+        const uint32_t c = cnt[a];
+        s += c;
+        ps += (c + 63) / 64;
+    }
+    uint32_t x = s, px = ps;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)x, o, 64), py = (uint32_t)__shfl_up((int)px, o, 64);
+        if (lane >= o) { x += y; px += py; }
+    }
+    if (lane == 63) wsum[wave] = make_uint2(x, px);
+    __syncthreads();
+    uint32_t run = x - s, prun = px - ps, all = 0, pall = 0;
+#pragma unroll
+    for (int w = 0; w < AL_T / 64; ++w) {
+        const uint2 v = wsum[w];
+        run += w < wave ? v.x : 0u;
+        prun += w < wave ? v.y : 0u;
+        all += v.x;
+        pall += v.y;
+    }
+    for (int64_t k = 0; k < per; ++k) {               // the same trip count in every lane
+        const int64_t a = b0 + k;
+        const uint32_t c = a < b1 ? cnt[a] : 0u, np = (c + 63) / 64;
+        if (a < b1) {
+            off[a] = run;
+            cnt[a] = run;
+            poff[a] = prun;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u)
+            if (u < np) panchor[prun + u] = (uint16_t)a;
+        for (unsigned long long hubs = __builtin_amdgcn_ballot_w64(np > 4); hubs; hubs &= hubs - 1) {
+            const int l = __builtin_ctzll(hubs);
+            const uint32_t p0 = (uint32_t)__builtin_amdgcn_readlane((int)prun, l);
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)np, l);
+            const uint32_t ha = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a, l);
+            for (uint32_t u = 4 + lane; u < n; u += 64) panchor[p0 + u] = (uint16_t)ha;
+        }
+        run += c;
+        prun += np;
+    }
+    if (tid == 0) {
+        off[na] = all;
+        poff[na] = pall;
+    }
 }
 
 // ----------------------------------------------------------------------------------------
@@ -433,22 +534,23 @@ hipError_t launch_anchor_encode(const varrate_shape& sh, const void* K, const vo
                                 const AnchorWs& w, hipStream_t st) {
     const int64_t Np = sh.n - sh.w, Nc = coded_count(sh), na = anchor_count(sh);
     const varrate_shape shc = coded_shape(sh);
-    const int64_t pieces = (Nc + sh.w + na) * sh.G;
-    anc_prep<uint16_t><<<(unsigned)((pieces + 3) / 4), 256, 0, st>>>(
+    const int64_t rows = Nc + sh.w + na;
+    // one workgroup per 64 rows and head: more threads than anchors, whose counts they clear
+    anc_prep<<<(unsigned)((rows + AP_ROWS - 1) / AP_ROWS * sh.G), 256, 0, st>>>(
         (const uint16_t*)K, (const uint16_t*)V, sbar, nn, Np, Nc, na, sh.w, sh.G, sh.anchor_stride, w.sbar_c,
-        (uint16_t*)w.Kr, (uint16_t*)w.Vr, (uint16_t*)c.k_anchor, (uint16_t*)c.v_anchor);
+        (uint16_t*)w.Kr, (uint16_t*)w.Vr, (uint16_t*)c.k_anchor, (uint16_t*)c.v_anchor, w.cnt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const uint32_t* csz = nullptr;
     if ((e = launch_allocate(shc, w.sbar_c, c, w.alloc, st, nullptr, &csz)) != hipSuccess) return e;
     if ((e = launch_project(shc, w.Kr, w.Vr, PK, PV, c, st, csz)) != hipSuccess) return e;
-    anc_zero<<<(unsigned)((na + 255) / 256), 256, 0, st>>>(w.cnt, na);
-    anc_count<<<(unsigned)((Nc + 255) / 256), 256, 0, st>>>(c.sidx, nn, Nc, c.snn, w.cnt);
-    anc_scan<<<1, 1024, 0, st>>>(w.cnt, na, c.inv_off);
-    anc_fill<<<(unsigned)((Nc + 255) / 256), 256, 0, st>>>(c.snn, Nc, w.cnt, c.inv_pos);
-    anc_pcount<<<(unsigned)((na + 255) / 256), 256, 0, st>>>(c.inv_off, na, w.cnt);
-    anc_scan<<<1, 1024, 0, st>>>(w.cnt, na, c.piece_off);
-    anc_pfill<<<(unsigned)((na + 255) / 256), 256, 0, st>>>(c.piece_off, na, c.piece_anchor);
+    const unsigned wgs = (unsigned)((Nc + AL_T - 1) / AL_T);
+    const size_t lds = na <= AL_LDS ? (size_t)na * 4 : 0;
+    if (lds) anc_count<true><<<wgs, AL_T, lds, st>>>(c.sidx, nn, Nc, na, c.snn, w.cnt);
+    else anc_count<false><<<wgs, AL_T, 0, st>>>(c.sidx, nn, Nc, na, c.snn, w.cnt);
+    anc_lists<<<1, AL_T, 0, st>>>(w.cnt, na, c.inv_off, c.piece_off, c.piece_anchor);
+    if (lds) anc_fill<true><<<wgs, AL_T, lds, st>>>(c.snn, Nc, na, w.cnt, c.inv_pos);
+    else anc_fill<false><<<wgs, AL_T, 0, st>>>(c.snn, Nc, na, w.cnt, c.inv_pos);
     return hipGetLastError();
 }
 

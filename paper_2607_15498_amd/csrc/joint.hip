@@ -193,8 +193,8 @@ __global__ __launch_bounds__(JP_T, 2) void jproj_kernel(const float* __restrict_
 // the coefficients up to the next multiple of 128 are computed for nothing.  W is split once
 // into bf16 hi and lo parts in fragment order (jprep_kernel), z rows are gathered straight into
 // the stages.  The products and their order per coefficient are those of jproj_kernel.  MFMA
-// bound: 32768-token Llama layer, R = 1024, 467 us (one tile per 256 consecutive tokens and 128 coefficients) before, 127 us now (920 TFLOP/s of
-// 117 GFLOP; 1.8 rounds of tiles over the CUs).
+// bound: 32768-token Llama layer, R = 1024, 467 us (one tile per 256 consecutive tokens and 128
+// coefficients) before, 127 us now (920 TFLOP/s of 117 GFLOP; 1.8 rounds of tiles over the CUs).
 struct JProj {
     const uint16_t* K;
     const uint16_t* V;

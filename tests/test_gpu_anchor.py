@@ -253,3 +253,52 @@ def test_anchor_end_to_end(vr, oracle_lib, name):
     say(f"[anchor end-to-end] {name}: rank mismatches {mism} of {shape.N}; worst decode rel err {worst:.3e}")
     assert mism <= max(8, shape.N // 1000)
     assert worst <= DEC_TOL_BF16
+
+
+@pytest.mark.parametrize("n_prefix,delta,kappa", [
+    (8, 2, 90), (64, 16, 60), (256, 2, 80), (257, 2, 80), (258, 2, 80), (520, 4, 60),
+    (16384, 4, 60), (16387, 4, 60), (25002, 2, 80)])
+def test_search_and_lists_at_tile_edges(vr, n_prefix, delta, kappa):
+    """The search at the edges of both its tile shapes and the inverse lists on both sides of the
+    count of anchors that fits LDS, on values whose distances are whole numbers exact in fp32:
+    many ties, which go to the lower anchor, so the anchors must match bit for bit."""
+    import torch
+    G, w = 1, 4
+    shape = vr.Shape(n=n_prefix + w, G=G, H=G, w=w, r_min=0, kappa_pct=kappa, dtype="bf16", anchor_stride=delta)
+    gen = torch.Generator(device="cuda").manual_seed(n_prefix)
+    draw = lambda: torch.randint(-2, 3, (n_prefix + w, G, 128), generator=gen, device="cuda").bfloat16()
+    K, V = draw(), draw()
+    K[::3] = K[0].clone()                                   # whole runs of equal keys
+    nn = vr.anchor_search(shape, K, V)
+    torch.cuda.synchronize()
+    tok = torch.arange(n_prefix, device="cuda")
+    anchors, coded = tok[::delta], tok[tok % delta != 0]
+    assert len(anchors) == shape.na and len(coded) == shape.N
+    z = torch.cat([K[:n_prefix, 0], V[:n_prefix, 0]], dim=1).double()
+    za = z[anchors]
+    for a in range(0, shape.N, 2048):
+        key = (za ** 2).sum(1)[None] - 2.0 * z[coded[a:a + 2048]] @ za.T
+        order = key * shape.na + torch.arange(shape.na, device="cuda")[None]     # unique, exact
+        want = order.topk(4, dim=1, largest=False, sorted=True).indices
+        assert bool((nn[a:a + 2048].long() & 0xFFFF).eq(want).all()), (n_prefix, a)
+    # anchor 0 and anchor 3 as hubs of every list, the others drawn
+    hubs = torch.randint(0, shape.na, (shape.N, 4), generator=gen, device="cuda")
+    hubs[:, 0], hubs[:, 1] = 0, 3
+    sbar = torch.rand(n_prefix, generator=gen, device="cuda")
+    eye = torch.eye(128, device="cuda")[None].contiguous()
+    c = vr.anchor_encode(shape, K, V, sbar, hubs.to(torch.int16), eye, eye)
+    torch.cuda.synchronize()
+    snn = c.snn.long() & 0xFFFF
+    assert bool((snn == hubs[c.sidx.long()]).all())
+    cnt = torch.bincount(snn.reshape(-1), minlength=shape.na)
+    off = c.inv_off.long()
+    assert bool((off[1:] - off[:-1] == cnt).all()) and int(off[0]) == 0
+    pieces = (cnt + 63) // 64
+    poff = c.piece_off.long()
+    assert bool((poff[1:] - poff[:-1] == pieces).all()) and int(poff[0]) == 0
+    got = c.piece_anchor.long()[:int(poff[-1])] & 0xFFFF
+    assert bool((got == torch.repeat_interleave(torch.arange(shape.na, device="cuda"), pieces)).all())
+    # each list holds its positions, in any order: (anchor, position) pairs sorted
+    pair = torch.repeat_interleave(torch.arange(shape.na, device="cuda"), cnt) * shape.N + c.inv_pos.long()
+    want = snn * shape.N + torch.arange(shape.N, device="cuda")[:, None]
+    assert bool((pair.sort().values == want.reshape(-1).sort().values).all())
