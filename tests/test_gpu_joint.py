@@ -224,3 +224,45 @@ def test_joint_projection_tile_edges(vr, N, G, R, kappa, r_min):
     got = c.coef.double()
     assert bool(((got[at] - ref[keep]).abs() <= ref[keep].abs() * 2.0 ** -7 + 2.0 ** -15 * S[keep]).all())
     assert bool((got[c.B:] == 0).all())
+
+
+@pytest.mark.parametrize("N,G,H,R,kappa,r_min,dtype,S,Q", [
+    (1, 1, 1, 256, 99, 0, "bf16", 1, 1), (16, 1, 2, 256, 60, 0, "f32", 1, 2), (31, 2, 2, 512, 80, 0, "bf16", 1, 3),
+    (33, 4, 28, 1024, 99, 16, "bf16", 1, 1), (129, 4, 28, 1024, 40, 0, "f32", 1, 1), (127, 4, 4, 768, 50, 1, "bf16", 2, 8),
+    (513, 4, 8, 1024, 99, 0, "bf16", 1, 4), (1000, 4, 8, 1024, 70, 128, "bf16", 3, 2), (2500, 4, 8, 768, 20, 0, "f32", 1, 4),
+    (4100, 4, 8, 1024, 95, 8, "bf16", 17, 1), (9000, 8, 32, 1024, 20, 0, "bf16", 1, 1)])
+def test_joint_decode_block_edges(vr, N, G, H, R, kappa, r_min, dtype, S, Q):
+    """The decode where its blocks (16, 32, 128 and 512 tokens), slices and row tiles end, with
+    budgets whose rows fill its load ring, tokens of rank 0 and more sequences than one launch
+    takes, against attention over the stored coefficients in 64 bits.  The score and value
+    products carry hi + lo parts (2^-16), so what is left is the output's rounding, 2^-9 in bf16;
+    1e-4 is the fp32 bar."""
+    import torch
+    w = 4
+    shape = vr.Shape(n=N + w, G=G, H=H, w=w, r_min=r_min, kappa_pct=kappa, dtype=dtype)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    dt = shape.torch_dtype
+    W = torch.linalg.qr(rnd(2 * G * 128, R).cpu()).Q.T.contiguous().cuda()
+    caches = []
+    for s in range(S):
+        Qw = (rnd(w, H, 128) * 2).to(dt)
+        K = rnd(N + w, G, 128) * (1 + 2 * (torch.rand((N + w, 1, 1), generator=gen, device="cuda") < 0.1))
+        caches.append(vr.joint_compress(shape, K.to(dt), rnd(N + w, G, 128).to(dt), Qw, W))
+    q = rnd(S, Q, H, 128).to(dt)
+    out = vr.joint_decode(shape, caches, q, W)
+    torch.cuda.synchronize()
+    hpg = H // G
+    for s in {0, S - 1}:
+        c = caches[s]
+        rank, off = c.rank.long()[:N], c.offset.long()
+        j = torch.arange(R, device="cuda")
+        keep = j[None] < rank[:, None]
+        z = torch.where(keep, c.coef.double()[torch.where(keep, off[:N, None] + j[None], 0)], 0.0) @ W.double()
+        for g in range(G):
+            k = torch.cat([z[:, g * 128:(g + 1) * 128], c.k_exact[g, :w].double()])
+            v = torch.cat([z[:, (G + g) * 128:(G + g + 1) * 128], c.v_exact[g, :w].double()])
+            for h in range(g * hpg, (g + 1) * hpg):
+                ref = (q[s, :, h].double() @ k.T / math.sqrt(128)).softmax(dim=1) @ v
+                err = float((out[s, :, h].double() - ref).abs().max() / ref.abs().max())
+                assert err <= (2.0 ** -8 if dtype == "bf16" else 1e-4), (s, h, err)
