@@ -1802,7 +1802,7 @@ constexpr int MG_COLS = 32;                       // output columns per workgrou
 constexpr int MG_CB = D / MG_COLS;                // column blocks per row
 constexpr int MG_RPT = 32;                        // coded records per thread in registers
 
-template <bool F32>
+template <bool F32, bool ANC>
 __global__ __launch_bounds__(MG_THREADS) void decode_merge_kernel(MergeParams p) {
     typedef typename Elem<F32>::T ET;
     __shared__ float wr[DC_MAX_REC];              // record weights exp(m_r - M)
@@ -1870,6 +1870,13 @@ __global__ __launch_bounds__(MG_THREADS) void decode_merge_kernel(MergeParams p)
 #pragma unroll
     for (int i = 0; i < 16; ++i) pb[i] = PV[(int64_t)(16 * jg + i) * D];
     const float ex = tid < MG_COLS ? recs[32 + row * D + MG_COLS * cb + tid] : 0.f;
+    // residual codec: original-space anchor records nrc + jg, + 8, .. (column c), the first four
+    // loaded here (a loop over all of them by the column's one thread: 11.7 us against 4.7 with 32)
+    const float* arec = recs + (int64_t)(nrc + jg) * DC_REC + 32 + row * D + MG_COLS * cb + c;
+    float ax[4];
+    if constexpr (ANC)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ax[u] = nrc + jg + 8 * u < nrec ? arec[(int64_t)(8 * u) * DC_REC] : 0.f;
 
     // ---- 2. row maximum over the records, record weights, softmax denominator
     float mx = fmaxf(tid < nrec ? ms[0] : -INFINITY, tid + MG_THREADS < nrec ? ms[1] : -INFINITY);
@@ -1925,14 +1932,20 @@ __global__ __launch_bounds__(MG_THREADS) void decode_merge_kernel(MergeParams p)
         const int jj = 16 * jg + i;
         o += (accR[0][jj] + accR[1][jj]) * pb[i];
     }
+    if constexpr (ANC) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (nrc + jg + 8 * u < nrec) o += wr[nrc + jg + 8 * u] * ax[u];
+#pragma unroll 4
+        for (int r = nrc + jg + 32; r < nrec; r += 8) o += wr[r] * arec[(int64_t)(r - nrc - jg) * DC_REC];
+    }
     part8[jg][c] = o;
     __syncthreads();
     if (tid < MG_COLS) {
         float t = part8[0][tid];
 #pragma unroll
         for (int k = 1; k < 8; ++k) t += part8[k][tid];
-        float e = wr[0] * ex;
-        for (int r = nrc; r < nrec; ++r) e += wr[r] * recs[(int64_t)r * DC_REC + 32 + row * D + MG_COLS * cb + tid];
+        const float e = wr[0] * ex;
         const float val = (t + e) / L;
         const int qrow = 16 * qt + row;
         const int query = qrow / p.hpg, hh = qrow % p.hpg;
@@ -2118,19 +2131,23 @@ __global__ __launch_bounds__(MG_THREADS) void decode_merge_rows_kernel(MergePara
 // Residual codec (Sec. 3.1 Eq. (2)): a coded token's key is its anchors' mean plus the
 // truncated projection, so its score is the mean of its 4 anchors' scores plus the rank-space
 // product, and its value's anchor part sends a quarter of its softmax weight to each of its
-// anchors.  Three more launches around the streaming kernel:
-//   anc_qscores  X[unit][a][row] = <q_row, k_a> / sqrt(d) for every anchor (exact rows)
+// anchors.  Four more launches around the streaming kernel:
+//   anc_qscores  X[unit][a][row] = <q_row, k_a> / sqrt(d) for every anchor (exact rows), and
+//                their maxima per 64 anchors
 //   anc_xbar     xbar[unit][pos][row] = (1/4) sum of X over the stored position's anchors, the
 //                term the streaming kernel adds to each coded score (it also writes the final
 //                scores S[unit][pos][row])
 //   anc_pieces   per piece of an anchor's list (64 entries): sum of exp(S - F)
-//   anc_weights  per anchor: W_a = exp(X_a - F) + (1/4) sum over the positions that use a
-//                of exp(S - F) (its pieces)
 //   anc_values   one record per (unit, block of anchors) in the original space: for its
-//                anchors, acc = sum W_a v_a, l = sum exp(X_a - F), m = F (a bound of every
+//                anchors, acc = sum W_a v_a with W_a = exp(X_a - F) + (1/4) sum over the
+//                positions that use a of exp(S - F), l = sum exp(X_a - F), m = F (a bound of every
 //                score involved); the merge combines these with the others by log-sum-exp
 //                like the exact record.
+// Consecutive workgroups take consecutive units, as in the streaming kernel, so with 8 KV heads a
+// unit's X, xbar and S stay in one XCD's L2 (workgroup L runs on XCD L mod 8): the six launches of
+// a 32768-token Llama layer 53.9 -> 46.8 us.
 struct AncDec {
+    int units;
     const varrate_cache* seq;   // unused on the device
     const void* q[DC_SEQ];
     const void* ka[DC_SEQ];
@@ -2143,7 +2160,6 @@ struct AncDec {
     float* X;          // [unit][na][ns]
     float* XM;         // [unit][ceil(na / 64)][ns] block maxima of X
     float* PW;         // [unit][np_bound][ns] per-piece sums of exp(S - F)
-    float* W;          // [unit][na][ns] anchor weights
     float* F;          // [unit][16] the frame
     int64_t np_bound;  // pieces per unit at most: 4 N / 64 + na
     float* xbar;       // [unit][16 total_tiles][ns]
@@ -2162,71 +2178,84 @@ __device__ __forceinline__ void anc_unit(const AncDec& p, int unit, int& sq, int
     rows = min(16, p.rows_total - 16 * qt);
 }
 
-// one thread per (anchor, row): 64 anchors x 4 row groups per workgroup
+// Four threads per anchor (a quarter of its key each), 64 anchors per workgroup, the query rows
+// in LDS; the block's maxima in the same launch.  One thread per (anchor, row) and a launch of
+// its own for the maxima: 5.4 + 3.6 us against 4.0 (Llama layer, 32768 tokens, Delta = 16).
 __global__ __launch_bounds__(256) void anc_qscores(AncDec p) {
+    __shared__ __attribute__((aligned(16))) float qs[16][D];
+    __shared__ float xm[4][16];
     const int blocks = (int)((p.na + 63) / 64);
-    const int unit = blockIdx.x / blocks, ab = blockIdx.x % blocks;
+    const int unit = blockIdx.x % p.units, ab = blockIdx.x / p.units;
     int sq, g, qt, rows;
     anc_unit(p, unit, sq, g, qt, rows);
-    const int64_t a = (int64_t)ab * 64 + (threadIdx.x >> 2);
-    const int rg = threadIdx.x & 3;
-    if (a >= p.na) return;
-    const uint16_t* ka = reinterpret_cast<const uint16_t*>(p.ka[sq]) + (a * p.G + g) * D;
+    const int tid = threadIdx.x, sub = tid & 3;
+    const int64_t a = (int64_t)ab * 64 + (tid >> 2);
+    const uint16_t* ka = reinterpret_cast<const uint16_t*>(p.ka[sq]) + (min(a, p.na - 1) * p.G + g) * D;
+    u32x4 kk[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) kk[c] = load16(ka + 8 * (sub + 4 * c));
     const uint16_t* qb = reinterpret_cast<const uint16_t*>(p.q[sq]);
+    for (int i = tid; i < p.ns * (D / 8); i += 256) {
+        const int r = i / (D / 8), e = 8 * (i % (D / 8)), qrow = 16 * qt + r;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (r < rows) v = load16(qb + ((int64_t)(qrow / p.hpg) * p.H + g * p.hpg + qrow % p.hpg) * D + e);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            qs[r][e + 2 * k] = bf_lo(v[k]);
+            qs[r][e + 2 * k + 1] = bf_hi(v[k]);
+        }
+    }
+    __syncthreads();
     float* X = p.X + ((int64_t)unit * p.na + a) * p.ns;
-    for (int r = rg; r < p.ns; r += 4) {
-        float acc = 0.f;
-        if (r < rows) {
-            const int qrow = 16 * qt + r;
-            const uint16_t* qv = qb + ((int64_t)(qrow / p.hpg) * p.H + g * p.hpg + qrow % p.hpg) * D;
-            for (int e = 0; e < D; e += 8) {
-                const u32x4 kk = load16(ka + e), qq = load16(qv + e);
+    for (int r4 = 0; r4 < p.ns; r4 += 4) {
+        float acc[4], mine = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc[r] = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float* qv = &qs[r4 + r][8 * (sub + 4 * c)];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    acc = fmaf(bf_lo(kk[k]), bf_lo(qq[k]), acc);
-                    acc = fmaf(bf_hi(kk[k]), bf_hi(qq[k]), acc);
+                    acc[r] = fmaf(bf_lo(kk[c][k]), qv[2 * k], acc[r]);
+                    acc[r] = fmaf(bf_hi(kk[c][k]), qv[2 * k + 1], acc[r]);
                 }
             }
+            acc[r] += shfl_xor_f(acc[r], 1);
+            acc[r] += shfl_xor_f(acc[r], 2);
+            mine = r == sub ? acc[r] : mine;
         }
-        X[r] = acc * 0.08838834764831845f;   // 1/sqrt(128)
+        mine *= 0.08838834764831845f;   // 1/sqrt(128)
+        if (a < p.na) X[r4 + sub] = mine;
+        float m = a < p.na ? mine : -INFINITY;
+        m = fmaxf(m, shfl_xor_f(m, 4));
+        m = xmax32(xmax16(fmaxf(m, shfl_xor_f(m, 8))));
+        if ((tid & 63) < 4) xm[tid >> 6][r4 + sub] = m;
     }
+    __syncthreads();
+    if (tid < p.ns)
+        p.XM[((int64_t)unit * blocks + ab) * p.ns + tid] = fmaxf(fmaxf(xm[0][tid], xm[1][tid]), fmaxf(xm[2][tid], xm[3][tid]));
 }
 
-// the block maxima of X (per row), for the frame of the anchor weights
-__global__ __launch_bounds__(256) void anc_xmax(AncDec p) {
-    const int blocks = (int)((p.na + 63) / 64);
-    const int unit = blockIdx.x / blocks, ab = blockIdx.x % blocks;
-    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;   // 4 waves: rows r, r + 4, ...
-    const int64_t a = (int64_t)ab * 64 + lane;
-    const float* X = p.X + (int64_t)unit * p.na * p.ns;
-    for (int rr = r; rr < p.ns; rr += 4) {
-        float m = a < p.na ? X[a * p.ns + rr] : -INFINITY;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-        if (lane == 0) p.XM[((int64_t)unit * blocks + ab) * p.ns + rr] = m;
-    }
-}
-
-// one thread per (stored position, row group)
+// one thread per (stored position, 4 rows)
 __global__ __launch_bounds__(256) void anc_xbar(AncDec p) {
-    const int npos = 16 * p.total_tiles;
-    const int blocks = (npos + 63) / 64;
-    const int unit = blockIdx.x / blocks, pb = blockIdx.x % blocks;
+    const int npos = 16 * p.total_tiles, n4 = p.ns / 4;
+    const int unit = blockIdx.x % p.units, i = blockIdx.x / p.units * 256 + threadIdx.x;
     int sq, g, qt, rows;
     anc_unit(p, unit, sq, g, qt, rows);
-    const int64_t pos = (int64_t)pb * 64 + (threadIdx.x >> 2);
-    const int rg = threadIdx.x & 3;
+    const int pos = i / n4, r4 = i % n4;
     if (pos >= npos) return;
-    float* xb = p.xbar + ((int64_t)unit * npos + pos) * p.ns;
-    const float* X = p.X + (int64_t)unit * p.na * p.ns;
+    f32x4* xb = reinterpret_cast<f32x4*>(p.xbar + ((int64_t)unit * npos + pos) * p.ns) + r4;
+    const f32x4* X = reinterpret_cast<const f32x4*>(p.X + (int64_t)unit * p.na * p.ns) + r4;
     if (pos >= p.N) {
-        for (int r = rg; r < p.ns; r += 4) xb[r] = 0.f;
+        *xb = f32x4{0.f, 0.f, 0.f, 0.f};
         return;
     }
-    const uint16_t* nn = p.snn[sq] + pos * 4;
-    const int64_t a0 = nn[0], a1 = nn[1], a2 = nn[2], a3 = nn[3];
-    for (int r = rg; r < p.ns; r += 4)
-        xb[r] = (((X[a0 * p.ns + r] + X[a1 * p.ns + r]) + X[a2 * p.ns + r]) + X[a3 * p.ns + r]) * 0.25f;
+    uint16_t nn[4];
+    __builtin_memcpy(nn, p.snn[sq] + (int64_t)pos * 4, 8);     // 2-byte aligned
+    const f32x4 x0 = X[(int64_t)nn[0] * n4], x1 = X[(int64_t)nn[1] * n4], x2 = X[(int64_t)nn[2] * n4],
+                x3 = X[(int64_t)nn[3] * n4];
+    *xb = (((x0 + x1) + x2) + x3) * 0.25f;
 }
 
 // The frame F[row] of the anchor weights: an upper bound of every score they involve, the
@@ -2243,8 +2272,12 @@ __device__ __forceinline__ void anc_frame(const AncDec& p, int unit, int rows, f
     const float* XM = p.XM + (int64_t)unit * xb * p.ns;
     float m = -INFINITY, mx = -INFINITY;
     if (r < rows) {
-        for (int x = k; x < p.rec0; x += 16) m = fmaxf(m, recs[(int64_t)x * DC_REC + r]);
-        for (int b = k; b < xb; b += 16) mx = fmaxf(mx, XM[b * p.ns + r]);
+        for (int x0 = k; x0 < p.rec0; x0 += 64)      // four loads at a time (a maximum may see one twice)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m = fmaxf(m, recs[(int64_t)min(x0 + 16 * u, p.rec0 - 1) * DC_REC + r]);
+        for (int b0 = k; b0 < xb; b0 += 64)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) mx = fmaxf(mx, XM[min(b0 + 16 * u, xb - 1) * p.ns + r]);
     }
     part_m[k][r] = m;
     part_x[k][r] = mx;
@@ -2261,179 +2294,172 @@ __device__ __forceinline__ void anc_frame(const AncDec& p, int unit, int rows, f
     __syncthreads();
 }
 
-// Four threads per list piece (at most 64 entries, 16 each, all loads in flight), then a
-// fixed two-step butterfly: PW[P][row] = sum over the piece of exp(S - F).  The first
-// workgroup of each unit also stores F for the kernels after it.
+// Four threads per list piece (at most 64 entries, every fourth to a thread, all loads in flight),
+// then a fixed two-step butterfly: PW[P][row] = sum over the piece of exp(S - F).  R4: the unit's
+// score rows in fours.  A chain of loads (piece, its anchor's offsets, entries, scores): the piece's
+// part of it goes out before the frame's, and code for the rows that there are only (15.5 us with
+// both in turn, 16 rows' code and each unit's workgroups over all XCDs, 13.5 without the first two,
+// 10.4 now; the score gathers, 64 lines per load, are 4 of it; Llama layer, 32768 tokens,
+// Delta = 16).  The first workgroup of each unit also stores F for the kernel after it.
 constexpr int AP_T = 256;
 constexpr int AP_PIECES = AP_T / 4;   // pieces per workgroup
+template <int R4>
 __global__ __launch_bounds__(AP_T) void anc_pieces(AncDec p) {
-    __shared__ float F_s[16];
-    const int blocks = (int)((p.np_bound + AP_PIECES - 1) / AP_PIECES);
-    const int unit = blockIdx.x / blocks, pb = blockIdx.x % blocks;
+    __shared__ __attribute__((aligned(16))) float F_s[16];
+    const int unit = blockIdx.x % p.units, pb = blockIdx.x / p.units;
     int sq, g, qt, rows;
     anc_unit(p, unit, sq, g, qt, rows);
-    anc_frame(p, unit, rows, F_s);
-    if (pb == 0 && threadIdx.x < 16) p.F[unit * 16 + threadIdx.x] = F_s[threadIdx.x];
     const int64_t P = (int64_t)pb * AP_PIECES + (threadIdx.x >> 2);
     const int sub = threadIdx.x & 3;
-    const uint32_t npieces = p.piece_off[sq][p.na];
-    // whole quads leave together, so the butterfly below sees all four lanes
-    if (P >= (int64_t)npieces) return;
-    const int ns = p.ns;
-    const uint32_t a = p.piece_anchor[sq][P];
-    const uint32_t j = (uint32_t)P - p.piece_off[sq][a];
-    const uint32_t e_end = p.inv_off[sq][a + 1];
-    const uint32_t e0 = min(p.inv_off[sq][a] + 64 * j + 16 * sub, e_end);
-    const uint32_t e1 = min(e0 + 16, e_end);
+    const bool ok = P < (int64_t)p.piece_off[sq][p.na];
+    uint32_t e0 = 0, e1 = 0;              // this thread's entries e0, e0 + 4, .. < e1
+    if (ok) {
+        const uint32_t a = p.piece_anchor[sq][P];
+        const uint32_t j = (uint32_t)P - p.piece_off[sq][a];
+        const uint32_t b = p.inv_off[sq][a] + 64 * j;
+        e1 = min(b + 64, p.inv_off[sq][a + 1]);
+        e0 = b + sub;
+    }
     const uint32_t* inv = p.inv_pos[sq];
-    const float* S = p.S + (int64_t)unit * 16 * p.total_tiles * ns;
-    float F[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) F[r] = F_s[r];
     uint32_t pos[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) pos[u] = e0 + u < e1 ? inv[e0 + u] : 0u;
-    float sh[16];
+    for (int u = 0; u < 16; ++u) pos[u] = e0 + 4 * u < e1 ? inv[e0 + 4 * u] : 0u;
+    anc_frame(p, unit, rows, F_s);
+    if (pb == 0 && threadIdx.x < 16) p.F[unit * 16 + threadIdx.x] = F_s[threadIdx.x];
+    if (!ok) return;                      // whole quads
+    const f32x4* S = reinterpret_cast<const f32x4*>(p.S + (int64_t)unit * 16 * p.total_tiles * (4 * R4));
+    f32x4* pw = reinterpret_cast<f32x4*>(p.PW + ((int64_t)unit * p.np_bound + P) * (4 * R4));
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sh[r] = 0.f;
+    for (int r4 = 0; r4 < R4; ++r4) {
+        f32x4 v[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const bool ok = e0 + u < e1;
-        const f32x4* sp = reinterpret_cast<const f32x4*>(S + (int64_t)pos[u] * ns);
+        for (int u = 0; u < 16; ++u) v[u] = S[(int64_t)pos[u] * R4 + r4];
+        f32x4 sh = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            if (4 * r4 < ns && ok) {
-                const f32x4 v = sp[r4];
+        for (int k = 0; k < 4; ++k) {
+            const float F = F_s[4 * r4 + k];
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (4 * r4 + k < rows) sh[4 * r4 + k] += fast_exp(v[k] - F[4 * r4 + k]);
-            }
+            for (int u = 0; u < 16; ++u) sh[k] += e0 + 4 * u < e1 ? fast_exp(v[u][k] - F) : 0.f;
+            sh[k] += shfl_xor_f(sh[k], 1);
+            sh[k] += shfl_xor_f(sh[k], 2);
+            if (4 * r4 + k >= rows) sh[k] = 0.f;
         }
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        if (r < ns) {
-            sh[r] += __shfl_xor(sh[r], 1, 64);
-            sh[r] += __shfl_xor(sh[r], 2, 64);
-        }
-    }
-    if (sub == 0) {
-        float* pw = p.PW + ((int64_t)unit * p.np_bound + P) * ns;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (r < ns) pw[r] = sh[r];
+        if (sub == 0) pw[r4] = sh;
     }
 }
 
-// A wave per anchor: W_a = exp(X_a - F) + (1/4) sum of its pieces' PW (lanes take every 64th
-// piece, then a fixed butterfly).  Writes W[unit][a][row] and the anchor's own mass
-// exp(X_a - F) over X (read only here, by the same lane).
-constexpr int AW_T = 256;
-__global__ __launch_bounds__(AW_T) void anc_weights(AncDec p) {
-    const int blocks = (int)((p.na + AW_T / 64 - 1) / (AW_T / 64));
-    const int unit = blockIdx.x / blocks, ab = blockIdx.x % blocks;
-    int sq, g, qt, rows;
-    anc_unit(p, unit, sq, g, qt, rows);
-    const int lane = threadIdx.x & 63;
-    const int64_t a = (int64_t)ab * (AW_T / 64) + (threadIdx.x >> 6);
-    if (a >= p.na) return;   // whole waves
-    const int ns = p.ns;
-    const uint32_t P0 = p.piece_off[sq][a], P1 = p.piece_off[sq][a + 1];
-    const float* PW = p.PW + (int64_t)unit * p.np_bound * ns;
-    float sh[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sh[r] = 0.f;
-    for (uint32_t P = P0 + lane; P < P1; P += 64) {
-        const f32x4* pw = reinterpret_cast<const f32x4*>(PW + (int64_t)P * ns);
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            if (4 * r4 < ns) {
-                const f32x4 v = pw[r4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) sh[4 * r4 + k] += v[k];
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        if (r < rows) {
-            float v = sh[r];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            sh[r] = v;
-        }
-    }
-    if (lane < ns) {
-        const int r = lane;
-        float shr = 0.f;
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) shr = rr == r ? sh[rr] : shr;
-        float* X = p.X + ((int64_t)unit * p.na + a) * ns;
-        const float own = r < rows ? fast_exp(X[r] - p.F[unit * 16 + r]) : 0.f;
-        X[r] = own;
-        p.W[((int64_t)unit * p.na + a) * ns + r] = r < rows ? own + 0.25f * shr : 0.f;
-    }
-}
-
-// A workgroup per (unit, block of AV_A anchors): the value sums over the block's anchors
-// (value rows and weights staged in LDS) and its record.
+// A workgroup per (unit, block of AV_A anchors): their weights W_a = exp(X_a - F) + (1/4) sum of
+// their pieces' PW (four threads per anchor, then a fixed butterfly), the value sums over the
+// block's anchors (value rows and weights in LDS) and its record.  Weights by a wave per anchor
+// in a launch of their own and sums over 16 rows whatever the unit's: 9.9 + 9.9 us against 4.6
+// (Llama layer, 32768 tokens, Delta = 16: 1.4 pieces per anchor, 4 rows).
 constexpr int AV_T = 256;
 constexpr int AV_A = 64;                          // anchors per workgroup
+template <int R4>
 __global__ __launch_bounds__(AV_T) void anc_values(AncDec p) {
-    __shared__ float red[16];
-    __shared__ float W[AV_A][17];
-    __shared__ float own_s[AV_A][17];
+    constexpr int NS = 4 * R4;
+    __shared__ float own_w[AV_T / 64][16];
+    __shared__ __attribute__((aligned(16))) float W[NS][AV_A + 4];
     __shared__ __attribute__((aligned(16))) uint16_t vrow[AV_A][D];
-    const int unit = blockIdx.x / p.n_ablk, ab = blockIdx.x % p.n_ablk;
+    const int unit = blockIdx.x % p.units, ab = blockIdx.x / p.units;
     int sq, g, qt, rows;
     anc_unit(p, unit, sq, g, qt, rows);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, sub = tid & 3, j = tid >> 2;
     const int64_t a_lo = (int64_t)ab * AV_A;
     const int nact = (int)min<int64_t>(AV_A, p.na - a_lo);
-    const int ns = p.ns;
-    // the block's value rows, weights and own masses into LDS (all loads in flight together)
+    const int64_t a = a_lo + min(j, nact - 1);
+    // every load that waits for nothing: pieces' range, the anchor's own scores, F, value rows
+    const uint32_t P0 = p.piece_off[sq][a], P1 = j < nact ? p.piece_off[sq][a + 1] : P0;
+    float x[R4], F[R4];
+#pragma unroll
+    for (int r4 = 0; r4 < R4; ++r4) {
+        x[r4] = p.X[((int64_t)unit * p.na + a) * NS + 4 * r4 + sub];
+        F[r4] = p.F[unit * 16 + 4 * r4 + sub];
+    }
     {
         const uint16_t* va = reinterpret_cast<const uint16_t*>(p.va[sq]);
-        for (int k = tid; k < nact * (D / 8); k += AV_T) {
-            const int j = k / (D / 8), e = 8 * (k % (D / 8));
-            *reinterpret_cast<u32x4*>(&vrow[j][e]) = load16(va + ((a_lo + j) * p.G + g) * D + e);
-        }
-        const float* Wg = p.W + ((int64_t)unit * p.na + a_lo) * ns;
-        const float* Og = p.X + ((int64_t)unit * p.na + a_lo) * ns;
-        for (int k = tid; k < AV_A * 16; k += AV_T) {
-            const int j = k >> 4, r = k & 15;
-            const bool ok = j < nact && r < ns;
-            W[j][r] = ok ? Wg[j * ns + r] : 0.f;
-            own_s[j][r] = ok ? Og[j * ns + r] : 0.f;
-        }
-    }
-    __syncthreads();
-    // the anchors' own softmax mass, in anchor order
-    if (tid < 16) {
-        float l = 0.f;
-        for (int j = 0; j < nact; ++j) l += own_s[j][tid];
-        red[tid] = l;
-    }
-    // ---- the value sums: thread -> column c, rows rh, rh + 2, ... (anchors in order)
-    const int c = tid & (D - 1), rh = tid >> 7;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < nact; ++j) {
-        const float v = bf16_to_f32(vrow[j][c]);
+        u32x4 v[AV_A * D / 8 / AV_T];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc[k] = fmaf(W[j][rh + 2 * k], v, acc[k]);
+        for (int i = 0; i < AV_A * D / 8 / AV_T; ++i) {
+            const int k = tid + AV_T * i;
+            v[i] = load16(va + ((a_lo + min(k / (D / 8), nact - 1)) * p.G + g) * D + 8 * (k % (D / 8)));
+        }
+#pragma unroll
+        for (int i = 0; i < AV_A * D / 8 / AV_T; ++i) {
+            const int k = tid + AV_T * i;
+            *reinterpret_cast<u32x4*>(&vrow[k / (D / 8)][8 * (k % (D / 8))]) = k / (D / 8) < nact ? v[i] : u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    // the pieces' sums: thread -> every fourth piece, four in flight
+    const f32x4* PW = reinterpret_cast<const f32x4*>(p.PW + (int64_t)unit * p.np_bound * NS);
+    f32x4 sh[R4];
+#pragma unroll
+    for (int r4 = 0; r4 < R4; ++r4) sh[r4] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (uint32_t P = P0 + sub; P < P1; P += 16) {
+        f32x4 w[4][R4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int r4 = 0; r4 < R4; ++r4) w[u][r4] = PW[(int64_t)min(P + 4 * u, P1 - 1) * R4 + r4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (P + 4 * u < P1)
+#pragma unroll
+                for (int r4 = 0; r4 < R4; ++r4) sh[r4] = sh[r4] + w[u][r4];
+    }
+#pragma unroll
+    for (int r4 = 0; r4 < R4; ++r4) {
+        float mine = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float v = sh[r4][k];
+            v += shfl_xor_f(v, 1);
+            v += shfl_xor_f(v, 2);
+            mine = k == sub ? v : mine;
+        }
+        const bool ok = j < nact && 4 * r4 + sub < rows;
+        float own = ok ? fast_exp(x[r4] - F[r4]) : 0.f;
+        W[4 * r4 + sub][j] = ok ? own + 0.25f * mine : 0.f;
+        own += shfl_xor_f(own, 4);
+        own = xsum32(xsum16(own + shfl_xor_f(own, 8)));
+        if ((tid & 63) < 4) own_w[tid >> 6][4 * r4 + sub] = own;
     }
     __syncthreads();
+    // ---- the value sums: thread -> column c, rows rh, rh + 2, ... (anchors in order; past the
+    // block's last, weights and value rows are 0)
+    const int c = tid & (D - 1), rh = tid >> 7;
+    float acc[NS / 2];
+#pragma unroll
+    for (int k = 0; k < NS / 2; ++k) acc[k] = 0.f;
+#pragma unroll 2
+    for (int jj = 0; jj < AV_A; jj += 4) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = bf16_to_f32(vrow[jj + e][c]);
+#pragma unroll
+        for (int k = 0; k < NS / 2; ++k) {
+            const f32x4 w = *reinterpret_cast<const f32x4*>(&W[rh + 2 * k][jj]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[k] = fmaf(w[e], v[e], acc[k]);
+        }
+    }
     // ---- the record: m = F, l = the anchors' own mass, acc in the original space
     float* rec = p.part + ((int64_t)unit * p.nrec + p.rec0 + ab) * DC_REC;
     if (tid < 16) {
         rec[tid] = tid < rows ? p.F[unit * 16 + tid] : -INFINITY;
-        rec[16 + tid] = tid < rows ? red[tid] : 0.f;
+        rec[16 + tid] = tid < rows ? ((own_w[0][tid] + own_w[1][tid]) + own_w[2][tid]) + own_w[3][tid] : 0.f;
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < NS / 2; ++k) {
         const int r = rh + 2 * k;
         if (r < ((rows + 3) & ~3)) rec[32 + r * D + c] = r < rows ? acc[k] : 0.f;
     }
+}
+
+template <int R4>
+static void launch_anc_tail(const AncDec& ad, int units, hipStream_t st) {
+    anc_pieces<R4><<<(unsigned)(units * ((ad.np_bound + AP_PIECES - 1) / AP_PIECES)), AP_T, 0, st>>>(ad);
+    anc_values<R4><<<(unsigned)(units * ad.n_ablk), AV_T, 0, st>>>(ad);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -2498,11 +2524,11 @@ bool decode_supported(const varrate_shape& sh, int S, int Q) {
 }
 
 // Residual codec buffers after the records: X [units][na][ns], xbar and S [units][16 tiles][ns],
-// XM [units][na / 64][ns], PW [units][pieces][ns], W [units][na][ns], F [units][16]
+// XM [units][na / 64][ns], PW [units][pieces][ns], F [units][16]
 static inline int64_t anc_np_bound(const DecPlan& pl, int64_t N) { return 4 * N / 64 + pl.na; }
 static size_t anc_dec_bytes(const DecPlan& pl, size_t units, int64_t N) {
     if (!pl.na) return 0;
-    return 2 * align256(units * pl.na * pl.ns * 4) + 2 * align256(units * 16 * (size_t)pl.total_tiles * pl.ns * 4) +
+    return align256(units * pl.na * pl.ns * 4) + 2 * align256(units * 16 * (size_t)pl.total_tiles * pl.ns * 4) +
            align256(units * ((pl.na + 63) / 64) * pl.ns * 4) + align256(units * anc_np_bound(pl, N) * pl.ns * 4) +
            align256(units * 16 * 4);
 }
@@ -2540,8 +2566,7 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
     if (pl.nrec > DC_MAX_REC) return hipErrorInvalidValue;
     float* part = (float*)ws;
     // residual codec: X, xbar and S after the records
-    float *Xb = nullptr, *xbarb = nullptr, *Sb = nullptr, *XMb = nullptr, *PWb = nullptr, *Wb = nullptr,
-          *Fb = nullptr;
+    float *Xb = nullptr, *xbarb = nullptr, *Sb = nullptr, *XMb = nullptr, *PWb = nullptr, *Fb = nullptr;
     const int64_t np_bound = anc_np_bound(pl, coded_count(sh));
     if (anc) {
         if (reuse_group_region) return hipErrorInvalidValue;   // no fixed scratch for it
@@ -2556,8 +2581,6 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
         b += align256(units_all * ((pl.na + 63) / 64) * pl.ns * 4);
         PWb = (float*)b;
         b += align256(units_all * np_bound * pl.ns * 4);
-        Wb = (float*)b;
-        b += align256(units_all * pl.na * pl.ns * 4);
         Fb = (float*)b;
     }
     // rotary keys: the basis fragments and the frequency table after the records, prepared
@@ -2625,6 +2648,7 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
             prm.xbar = xbarb + u0 * 16 * pl.total_tiles * pl.ns;
             prm.S = Sb + u0 * 16 * pl.total_tiles * pl.ns;
             ad.seq = nullptr;
+            ad.units = prm.units;
             for (int i = 0; i < DC_SEQ; ++i) {
                 const int si = s0 + (i < ns ? i : 0);
                 const varrate_cache& c = caches[si];
@@ -2640,7 +2664,6 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
             ad.X = Xb + u0 * pl.na * pl.ns;
             ad.XM = XMb + u0 * ((pl.na + 63) / 64) * pl.ns;
             ad.PW = PWb + u0 * np_bound * pl.ns;
-            ad.W = Wb + u0 * pl.na * pl.ns;
             ad.F = Fb + u0 * 16;
             ad.np_bound = np_bound;
             ad.xbar = const_cast<float*>(prm.xbar);
@@ -2660,8 +2683,7 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
             ad.ablk = AV_A;
             ad.n_ablk = pl.n_ablk;
             anc_qscores<<<(unsigned)(prm.units * ((pl.na + 63) / 64)), 256, 0, st>>>(ad);
-            anc_xmax<<<(unsigned)(prm.units * ((pl.na + 63) / 64)), 256, 0, st>>>(ad);
-            anc_xbar<<<(unsigned)(prm.units * ((16 * pl.total_tiles + 63) / 64)), 256, 0, st>>>(ad);
+            anc_xbar<<<(unsigned)(prm.units * ((16 * pl.total_tiles * (pl.ns / 4) + 255) / 256)), 256, 0, st>>>(ad);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -2687,9 +2709,12 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (pl.na) {
-            anc_pieces<<<(unsigned)(prm.units * ((np_bound + AP_PIECES - 1) / AP_PIECES)), AP_T, 0, st>>>(ad);
-            anc_weights<<<(unsigned)(prm.units * ((pl.na + AW_T / 64 - 1) / (AW_T / 64))), AW_T, 0, st>>>(ad);
-            anc_values<<<(unsigned)(prm.units * pl.n_ablk), AV_T, 0, st>>>(ad);
+            switch (pl.ns) {
+                case 4: launch_anc_tail<1>(ad, prm.units, st); break;
+                case 8: launch_anc_tail<2>(ad, prm.units, st); break;
+                case 12: launch_anc_tail<3>(ad, prm.units, st); break;
+                default: launch_anc_tail<4>(ad, prm.units, st); break;
+            }
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -2722,9 +2747,10 @@ hipError_t launch_decode(const varrate_shape& sh, const varrate_cache* caches, i
             if (sh.dtype == VARRATE_BF16) decode_merge_rows_kernel<false><<<nmerge, MG_THREADS, 0, st>>>(mp);
             else decode_merge_rows_kernel<true><<<nmerge, MG_THREADS, 0, st>>>(mp);
         } else if (sh.dtype == VARRATE_BF16) {
-            decode_merge_kernel<false><<<nmerge, MG_THREADS, 0, st>>>(mp);
+            if (anc) decode_merge_kernel<false, true><<<nmerge, MG_THREADS, 0, st>>>(mp);
+            else decode_merge_kernel<false, false><<<nmerge, MG_THREADS, 0, st>>>(mp);
         } else {
-            decode_merge_kernel<true><<<nmerge, MG_THREADS, 0, st>>>(mp);
+            decode_merge_kernel<true, false><<<nmerge, MG_THREADS, 0, st>>>(mp);
         }
         e = hipGetLastError();
         if (e != hipSuccess) return e;

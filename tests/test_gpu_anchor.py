@@ -302,3 +302,36 @@ def test_search_and_lists_at_tile_edges(vr, n_prefix, delta, kappa):
     pair = torch.repeat_interleave(torch.arange(shape.na, device="cuda"), cnt) * shape.N + c.inv_pos.long()
     want = snn * shape.N + torch.arange(shape.N, device="cuda")[:, None]
     assert bool((pair.sort().values == want.reshape(-1).sort().values).all())
+
+
+@pytest.mark.parametrize("n,Q,hubs", [(1060, 1, False), (1300, 3, False), (1300, 6, False), (4200, 4, True), (9000, 2, True)])
+def test_anchor_decode_rows_and_hubs(vr, oracle_lib, n, Q, hubs):
+    """The anchor side where its launches are specialised: 3, 9, 12 and 18 query rows (score rows
+    in fours, a second row tile of two rows), a last block of few anchors (65 and 80 of them, with
+    the merge's record loop past its first 32 blocks' worth at 9000 tokens), and four anchors that
+    are nearest to every token, with lists of up to 130 pieces."""
+    import torch
+    from workloads import CONFIGS, make_layer
+    cfg = dict(CONFIGS["llama_32k"])
+    cfg.update(n=n, G=2, H=6, seed=n)
+    delta = 4 if n == 9000 else DELTA
+    kappa = 60 if n == 9000 else 30
+    li = make_layer(cfg, n_queries=Q)
+    K, V = li.K.copy(), li.V.copy()
+    if hubs:
+        far = np.arange(4 * delta, n - 32, delta)
+        K[far] = (3.0 * K[far]).astype(K.dtype)
+        V[far] = (3.0 * V[far]).astype(V.dtype)
+        K, V = (host(dev(x, torch.bfloat16)).astype(np.float32) for x in (K, V))
+    shape = vr.Shape(n=n, G=2, H=6, w=32, r_min=16, kappa_pct=kappa, dtype="bf16", anchor_stride=delta)
+    ac = oracle_lib.compress_anchor(K, V, li.Qw, li.PK, li.PV, 6, kappa, 16, "bf16", delta=delta)
+    if hubs:
+        assert np.bincount(ac.nn.ravel()).max() > 0.5 * len(ac.nn)
+    PK, PV = dev(li.PK, torch.float32), dev(li.PV, torch.float32)
+    cache = vr.anchor_encode(shape, dev(K, torch.bfloat16), dev(V, torch.bfloat16), dev(ac.sbar, torch.float32),
+                             dev(ac.nn.astype(np.int16), torch.int16), PK, PV)
+    out = host(vr.decode(shape, [cache], dev(li.q, torch.bfloat16), PK, PV))
+    torch.cuda.synchronize()
+    worst = max(decode_err(out[i], oracle_lib.decode_anchor(ac, li.PK, li.PV, li.q[i], 6)) for i in range(Q))
+    say(f"[anchor decode rows] n={n} queries={Q} hubs={hubs}: worst rel err {worst:.3e}")
+    assert worst <= DEC_TOL_BF16
