@@ -71,12 +71,13 @@ __global__ __launch_bounds__(256) void anc_norms(const uint16_t* __restrict__ K,
 // high words are the fp32 keys and whose low words are the anchor numbers (complemented under
 // a negative key): doubles order by sign, then by the remaining 63 bits, so they order as
 // (key, anchor) pairs do and a compare-exchange is one minimum and one maximum.  An fp32
-// infinity is a finite double there (a NaN key counts as one); the largest pattern used,
-// AN_NONE, stands for no anchor.
+// infinity is a finite double there; NaN keys come behind it, whatever their payload, and the
+// largest pattern used, AN_NONE, stands for no anchor.
 typedef double Top4[AN_C];
-constexpr unsigned long long AN_NONE = 0x7F800000FFFFFFFFull;     // key +inf
+constexpr uint32_t AN_NAN = 0x7F800001u;                          // high word of a NaN key
+constexpr unsigned long long AN_NONE = ((unsigned long long)AN_NAN << 32) | 0xFFFFFFFFull;
 __device__ __forceinline__ double anc_pack(float key, uint32_t a) {
-    const uint32_t k = __float_as_uint(key);
+    const uint32_t k = key == key ? __float_as_uint(key) : AN_NAN;
     const uint32_t lo = a ^ (uint32_t)((int32_t)k >> 31);
     return __builtin_bit_cast(double, ((unsigned long long)k << 32) | lo);
 }
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(512, 2) void anc_search(AnSearch p) {
     const int steps = 2 * p.GD / 64;
     f32x4 acc[CF][TF];                        // [anchor tile][token tile] of this wave
     gemm_tile<TF, CF, false>(smem, tok, anc, jump, steps, acc);
-    // the lane's anchors and their norms (absent anchors, numbers na and up: +inf keys, behind
+    // the lane's anchors and their norms (absent anchors, numbers na and up: NaN keys, behind
     // every real anchor's, of which there are at least four)
     float nrm[CF][4];
 #pragma unroll
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(512, 2) void anc_search(AnSearch p) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int64_t a = a0 + 16 * (CF * wa + j) + 4 * grp + v;
-            nrm[j][v] = a < p.na ? p.nrm[a] : INFINITY;
+            nrm[j][v] = a < p.na ? p.nrm[a] : NAN;
         }
     double* xt = reinterpret_cast<double*>(smem);              // [wt][TF token tiles][16][4]
     const uint32_t an = (uint32_t)(a0 + 16 * CF * wa + 4 * grp);
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(512, 2) void anc_search(AnSearch p) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const uint32_t a = an + 16 * j + v;
-                o[v] = anc_pack(fminf(nrm[j][v] - 2.f * acc[j][c][v], INFINITY), a);
+                o[v] = anc_pack(nrm[j][v] - 2.f * acc[j][c][v], a);
             }
             top4_sort(o);
             if (j == 0) {

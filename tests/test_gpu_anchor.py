@@ -335,3 +335,28 @@ def test_anchor_decode_rows_and_hubs(vr, oracle_lib, n, Q, hubs):
     worst = max(decode_err(out[i], oracle_lib.decode_anchor(ac, li.PK, li.PV, li.q[i], 6)) for i in range(Q))
     say(f"[anchor decode rows] n={n} queries={Q} hubs={hubs}: worst rel err {worst:.3e}")
     assert worst <= DEC_TOL_BF16
+
+
+@pytest.mark.parametrize("n_prefix,delta,kappa", [(10, 2, 95), (16384, 4, 60)])
+def test_search_orders_zero_infinite_and_nan_keys(vr, n_prefix, delta, kappa):
+    """Keys of 0 (anchors of zeros), of infinity (norms past fp32) and NaN (a NaN in the anchor),
+    by both tile shapes: the zeros first, then the infinite ones, ties to the lower number, and
+    no NaN while there are others (its mean would make the token's coefficients NaN)."""
+    import torch
+    w = 4
+    shape = vr.Shape(n=n_prefix + w, G=1, H=1, w=w, r_min=0, kappa_pct=kappa, dtype="bf16", anchor_stride=delta)
+    gen = torch.Generator(device="cuda").manual_seed(n_prefix)
+    draw = lambda: torch.randint(-2, 3, (n_prefix + w, 1, 128), generator=gen, device="cuda").bfloat16()
+    K, V = draw(), draw()
+    K[:n_prefix:delta] = 2.0 ** 66
+    zero = [1, shape.na - 2]
+    for a in zero:
+        K[a * delta] = 0.0
+        V[a * delta] = 0.0
+    nan = [0, 2] if shape.na > 5 else [0]
+    for a in nan:
+        V[a * delta, 0, 77] = float("nan")
+    nn = vr.anchor_search(shape, K, V).long() & 0xFFFF
+    torch.cuda.synchronize()
+    far = [a for a in range(shape.na) if a not in zero + nan][:2]
+    assert bool((nn == torch.tensor(zero + far, device="cuda")).all()), nn.unique(dim=0)
