@@ -28,6 +28,14 @@ namespace vr {
 constexpr int AN_C = 4;                 // nearest anchors per coded token
 constexpr int AN_TA = 128;              // anchors per search tile at least (32 CF)
 
+// A token's four anchor numbers in the caller's lists, which are 2-byte aligned.
+__device__ __forceinline__ uint2 anc_near(const uint16_t* p) {
+    uint2 v;
+    __builtin_memcpy(&v, p, 8);
+    return v;
+}
+__device__ __forceinline__ void anc_near_out(uint16_t* p, uint2 v) { __builtin_memcpy(p, &v, 8); }
+
 __host__ __device__ inline int64_t anc_token(int64_t i, int delta) { return i + i / (delta - 1) + 1; }
 
 // ---- anchor norms: one wave per anchor, its row staged in LDS by 16-byte loads and summed
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(256) void anc_merge(const double* __restrict__ part
     uint2 out;
     out.x = pack2(anc_number(t[0]) & 0xFFFFu, anc_number(t[1]) & 0xFFFFu);
     out.y = pack2(anc_number(t[2]) & 0xFFFFu, anc_number(t[3]) & 0xFFFFu);
-    *reinterpret_cast<uint2*>(nn + i * AN_C) = out;
+    anc_near_out(nn + i * AN_C, out);
 }
 
 // ---- compaction, residuals and the anchor store.  A workgroup per (64 rows, head), 16 lanes
@@ -294,7 +302,7 @@ __global__ __launch_bounds__(256) void anc_prep(const uint16_t* __restrict__ K, 
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int64_t r = r0 + 16 * k;
-        near[k] = *reinterpret_cast<const uint2*>(nn + (r < Nc ? r : 0) * AN_C);
+        near[k] = anc_near(nn + (r < Nc ? r : 0) * AN_C);
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -358,8 +366,8 @@ __global__ __launch_bounds__(AL_T) void anc_count(const uint32_t* __restrict__ s
         __syncthreads();
     }
     if (p < Nc) {
-        const uint2 q = *reinterpret_cast<const uint2*>(nn + i * AN_C);
-        *reinterpret_cast<uint2*>(snn + p * AN_C) = q;
+        const uint2 q = anc_near(nn + i * AN_C);
+        anc_near_out(snn + p * AN_C, q);
         uint32_t* dst = LDS ? hist : cnt;
         atomicAdd(&dst[q.x & 0xFFFFu], 1u);
         atomicAdd(&dst[q.x >> 16], 1u);
@@ -380,7 +388,7 @@ __global__ __launch_bounds__(AL_T) void anc_fill(const uint16_t* __restrict__ sn
     const int tid = threadIdx.x;
     const int64_t p = (int64_t)blockIdx.x * AL_T + tid;
     const bool in = p < Nc;
-    const uint2 q = *reinterpret_cast<const uint2*>(snn + (in ? p : 0) * AN_C);
+    const uint2 q = anc_near(snn + (in ? p : 0) * AN_C);
     const uint32_t a4[AN_C] = {q.x & 0xFFFFu, q.x >> 16, q.y & 0xFFFFu, q.y >> 16};
     if constexpr (LDS) {
         uint32_t slot[AN_C];

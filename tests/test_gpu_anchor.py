@@ -360,3 +360,32 @@ def test_search_orders_zero_infinite_and_nan_keys(vr, n_prefix, delta, kappa):
     torch.cuda.synchronize()
     far = [a for a in range(shape.na) if a not in zero + nan][:2]
     assert bool((nn == torch.tensor(zero + far, device="cuda")).all()), nn.unique(dim=0)
+
+
+def test_neighbour_lists_at_any_element(vr):
+    """The callers' neighbour lists (int16, [N][4]) are taken wherever an element may lie: one
+    element past a 16-byte address as at one, for the lists given, kept and read by the decode."""
+    import torch
+    shape = vr.Shape(n=1300, G=2, H=8, w=32, r_min=0, kappa_pct=40, dtype="bf16", anchor_stride=DELTA)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    K, V, q = rnd(1300, 2, 128).bfloat16(), rnd(1300, 2, 128).bfloat16(), rnd(1, 8, 128).bfloat16()
+    eye = torch.eye(128, device="cuda").expand(2, 128, 128).contiguous()
+    sbar = torch.rand(1300 - 32, generator=gen, device="cuda")
+    nn = vr.anchor_search(shape, K, V)
+    outs = []
+    for at in (0, 1):
+        near = torch.zeros(4 * shape.N + 1, dtype=torch.int16, device="cuda")[at:at + 4 * shape.N].view(shape.N, 4)
+        near.copy_(nn)
+        cache = vr.new_cache(shape)
+        cache.snn = torch.zeros(4 * shape.N + 1, dtype=torch.int16, device="cuda")[at:at + 4 * shape.N].view(shape.N, 4)
+        assert near.data_ptr() % 16 == cache.snn.data_ptr() % 16 == 2 * at
+        vr.anchor_encode(shape, K, V, sbar, near, eye, eye, cache=cache)
+        outs.append((cache, vr.decode(shape, [cache], q, eye, eye).float()))
+    torch.cuda.synchronize()
+    (a, oa), (b, ob) = outs
+    assert bool((a.snn == nn[a.sidx.long()]).all())
+    for x in ("snn", "rank", "coef_k", "coef_v", "inv_off", "piece_off"):
+        assert torch.equal(getattr(a, x), getattr(b, x)), x
+    # the lists' entries, and so the order of a sum, are in any order: one rounding of the output
+    assert float((oa - ob).abs().max() / oa.abs().max()) <= 2.0 ** -8
