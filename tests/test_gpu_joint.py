@@ -266,3 +266,13 @@ def test_joint_decode_block_edges(vr, N, G, H, R, kappa, r_min, dtype, S, Q):
                 ref = (q[s, :, h].double() @ k.T / math.sqrt(128)).softmax(dim=1) @ v
                 err = float((out[s, :, h].double() - ref).abs().max() / ref.abs().max())
                 assert err <= (2.0 ** -8 if dtype == "bf16" else 1e-4), (s, h, err)
+
+
+@pytest.mark.parametrize("N,G,R,kappa,r_min", [
+    (24576, 1, 256, 70, 0), (24577, 1, 256, 70, 16), (16895, 2, 512, 60, 0), (12033, 4, 1024, 99, 0),
+    (12033, 4, 1024, 80, 0), (16896, 1, 256, 95, 8), (16896, 1, 256, 96, 8)])
+def test_joint_projection_wide_tiles(vr, N, G, R, kappa, r_min):
+    """The 256-token tiles where they and the lists end (a multiple, one past and one short of it,
+    every token at full rank), and on the sides of the rule that takes them: 310 and 376, 128 and
+    129 of them by its estimate."""
+    test_joint_projection_tile_edges(vr, N, G, R, kappa, r_min)
