@@ -274,17 +274,17 @@ JointLists joint_lists(const varrate_shape& sh, int R, uint8_t* ws) {
 
 // 256-token tiles reuse W best, but one fills a CU where two of the 64-token tiles share it: up to
 // 128 wide tiles the 512 or fewer narrow ones all run at once and are the faster, and so they are
-// where wide tiles leave a second round that is less than a quarter full.  The lists' lengths are
-// known on the device only; estimated here as B / 128 rows, 5/8 of a row for every token below the
-// cap R, and half a tile per list.  Whole compressions with either shape forced (R = 256 and 1024,
-// 10 to 40%, 1K to 32K tokens), narrow / wide us: 4 KV heads 104 / 118 at 84 wide tiles, 118 / 128
-// at 112, 129 / 126 at 140, 146 / 134 at 240, 157 / 159 at 300, 166 / 161 at 360; 8 KV heads
+// (from 8 KV heads on: 32 steps a tile) where wide tiles leave a second round that is less than a
+// quarter full.  The lists' lengths are known on the device only; estimated here as B / 128 rows,
+// 5/8 of a row for every token below the cap R, and half a tile per list.  Whole compressions with
+// either shape forced (R = 256 and 1024, 10 to 40%, 1K to 32K tokens), narrow / wide us: 4 KV heads
+// 104 / 118 at 84 wide tiles, 118 / 128 at 112, 129 / 126 at 140, 146 / 134 at 240, 172 / 170 at 292, 166 / 161 at 360; 8 KV heads
 // 103 / 121 at 114, 107 / 121 at 124, 129 / 123 at 149, 143 / 130 at 238, 167 / 175 at 266,
-// 177 / 184 at 295, 189 / 187 at 355, 233 / 201 at 473.  By tokens instead (wide past 12288)
+// 181 / 184 at 295, 189 / 187 at 355, 233 / 201 at 473.  By tokens instead (wide past 12288)
 // R = 256 lost up to 18 us at 16384 tokens.
-static bool joint_wide(int64_t N, int64_t B, int R) {
+static bool joint_wide(int64_t N, int64_t B, int R, int G) {
     const int64_t tiles = (B / 128 + (N - B / R) * 5 / 8) / 256 + R / 256;
-    return tiles > 128 && (tiles <= 256 || tiles > 320);
+    return tiles > 128 && (tiles <= 256 || tiles > 320 || G < 8);
 }
 
 template <int TF>
@@ -330,7 +330,7 @@ hipError_t launch_joint_project(const varrate_shape& sh, int R, const void* K, c
     p.N = N;
     p.G = sh.G;
     p.nb = l.nb;
-    return joint_wide(N, c.B, R) ? launch_jgemm<4>(p, st) : launch_jgemm<1>(p, st);
+    return joint_wide(N, c.B, R, sh.G) ? launch_jgemm<4>(p, st) : launch_jgemm<1>(p, st);
 }
 
 }  // namespace vr
