@@ -529,9 +529,12 @@ hipError_t launch_anchor_search(const varrate_shape& sh, const void* K, const vo
     p.na = na;
     p.delta = sh.anchor_stride;
     p.GD = GD;
-    // 256 x 256 tiles do the most per LDS byte; 64 tokens x 128 anchors where those would leave
-    // CUs idle
-    const bool wide = (Nc + 255) / 256 * ((na + 255) / 256) >= 192;
+    // 256 x 256 tiles do the most per LDS byte, but one fills a CU where two of 64 tokens x 128
+    // anchors share it: narrow ones are the faster as long as two rounds of 512 hold them all.
+    // Whole compressions with either shape forced, narrow / wide us: 4 KV heads 126 / 129 at 864
+    // narrow tiles, 143 / 144 at 1020, 155 / 151 at 1080, 134 / 129 at 1134; 8 KV heads 142 / 148,
+    // 166 / 169, 178 / 169, 161 / 152
+    const bool wide = (Nc + 63) / 64 * ((na + 127) / 128) > 1024;
     hipError_t e = wide ? launch_search<4, 8>(p, st) : launch_search<1, 4>(p, st);
     if (e != hipSuccess) return e;
     anc_merge<<<(unsigned)((Nc + 255) / 256), 256, 0, st>>>(w.part, Nc, p.n_atiles, nn);

@@ -389,3 +389,9 @@ def test_neighbour_lists_at_any_element(vr):
         assert torch.equal(getattr(a, x), getattr(b, x)), x
     # the lists' entries, and so the order of a sum, are in any order: one rounding of the output
     assert float((oa - ob).abs().max() / oa.abs().max()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("n_prefix,delta,kappa", [(11600, 16, 60), (11650, 16, 60)])
+def test_search_on_both_sides_of_the_tile_rule(vr, n_prefix, delta, kappa):
+    """1020 and 1026 narrow tiles' worth, which the narrow and the wide tiles take."""
+    test_search_and_lists_at_tile_edges(vr, n_prefix, delta, kappa)
