@@ -230,11 +230,12 @@ def test_joint_projection_tile_edges(vr, N, G, R, kappa, r_min):
     (1, 1, 1, 256, 99, 0, "bf16", 1, 1), (16, 1, 2, 256, 60, 0, "f32", 1, 2), (31, 2, 2, 512, 80, 0, "bf16", 1, 3),
     (33, 4, 28, 1024, 99, 16, "bf16", 1, 1), (129, 4, 28, 1024, 40, 0, "f32", 1, 1), (127, 4, 4, 768, 50, 1, "bf16", 2, 8),
     (513, 4, 8, 1024, 99, 0, "bf16", 1, 4), (1000, 4, 8, 1024, 70, 128, "bf16", 3, 2), (2500, 4, 8, 768, 20, 0, "f32", 1, 4),
-    (4100, 4, 8, 1024, 95, 8, "bf16", 17, 1), (9000, 8, 32, 1024, 20, 0, "bf16", 1, 1)])
+    (4100, 4, 8, 1024, 95, 8, "bf16", 17, 1), (9000, 8, 32, 1024, 20, 0, "bf16", 1, 1),
+    (96, 1, 2, 256, 4, 0, "bf16", 1, 1), (200, 4, 8, 1024, 99, 0, "f32", 1, 2), (150, 4, 28, 1024, 99, 0, "f32", 1, 1)])
 def test_joint_decode_block_edges(vr, N, G, H, R, kappa, r_min, dtype, S, Q):
     """The decode where its blocks (16, 32, 128 and 512 tokens), slices and row tiles end, with
-    budgets whose rows fill its load ring, tokens of rank 0 and more sequences than one launch
-    takes, against attention over the stored coefficients in 64 bits.  The score and value
+    budgets whose rows fill its load ring and one of nothing, tokens of rank 0 and more sequences
+    than one launch takes, against attention over the stored coefficients in 64 bits.  The score and value
     products carry hi + lo parts (2^-16), so what is left is the output's rounding, 2^-9 in bf16;
     1e-4 is the fp32 bar."""
     import torch

@@ -333,3 +333,46 @@ def test_codes_of_extreme_values(vr, bits, N, top):
     for kind in ("K", "V"):
         assert np.array_equal(codes[kind], k), kind
         assert np.array_equal(np.where(used, scales[kind], 0), np.where(used, sc, 0)), kind
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+def test_codes_of_infinities_and_nan(vr, bits):
+    """Groups holding infinities or NaN beside plain ones: a NaN leaves the group's absmax alone
+    and takes the lowest code, an infinity makes the scale infinite, under which finite values
+    code 0 and the infinity (inf / inf) the lowest code; the other groups of the tile are
+    unaffected.  Bit for bit against the definition with C's fmax and fmin."""
+    import torch
+    N, G, w = 300, 2, 1
+    shape = vr.Shape(n=N + w, G=G, H=G, w=w, r_min=0, kappa_pct=99, dtype="bf16")
+    cache, qc = vr.new_cache(shape), vr.new_qcache(shape, bits)
+    rng = np.random.default_rng(bits)
+    rank = rng.integers(60, 121, N)
+    srank, sidx, chunk_off = layout(rank, N)
+    coef = rng.standard_normal((N, G, 128)).astype(np.float32)
+    odd = rng.random((N, G, 128))
+    odd[::2] = 1.0                                   # whole tokens of plain groups between
+    for at, value in ((0.002, np.nan), (0.004, np.inf), (0.006, -np.inf), (0.008, -np.nan)):
+        coef[(odd < at) & (odd >= at - 0.002)] = value
+    coef[1, :, 32:64] = np.nan                       # a group of nothing else
+    coef = torch.from_numpy(coef).to(torch.bfloat16).float().numpy()
+    for kind, st in (("K", cache.coef_k), ("V", cache.coef_v)):
+        st.copy_(pack(coef, srank, sidx, chunk_off, N, kind, cache.coef_stride))
+    cache.srank.copy_(torch.from_numpy(srank.astype(np.uint8)))
+    cache.sidx.copy_(torch.from_numpy(sidx.astype(np.int32)))
+    cache.chunk_off.copy_(torch.from_numpy(chunk_off.astype(np.int32)))
+    vr.quantize(shape, cache, bits, qcache=qc)
+    torch.cuda.synchronize()
+    qmax = 2 ** (bits - 1) - 1
+    keep = np.arange(128)[None, None, :] < rank[:, None, None]
+    x = np.where(keep, coef, np.float32(0)).reshape(N, G, 4, 32)
+    assert np.isnan(x).any() and np.isinf(x).any()
+    with np.errstate(invalid="ignore", divide="ignore", over="ignore"):
+        sc = (np.fmax.reduce(np.abs(x), axis=3, initial=0) / np.float32(qmax)).astype(np.float16).astype(np.float32)
+        k = np.fmin(np.fmax(np.rint((x / sc[..., None]).astype(np.float32)), -qmax), qmax)
+    k = np.where(sc[..., None] == 0, 0, k).astype(np.int64).reshape(N, G, 128)
+    used = (np.arange(4)[None, :] * 32 < rank[:, None])[:, None, :]
+    qoff = qc.qchunk_off.cpu().numpy().astype(np.int64)
+    for kind, st in (("K", qc.code_k), ("V", qc.code_v)):
+        codes, scales = unpack_codes(st.cpu().numpy(), qoff, srank, sidx, N, kind, bits)
+        assert np.array_equal(codes, k), kind
+        assert np.array_equal(np.where(used, scales, 0), np.where(used, sc, 0)), kind
