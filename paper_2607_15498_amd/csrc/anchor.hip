@@ -9,9 +9,9 @@
 //
 //   anc_norms    ||z_a||^2 of every anchor (fp32, fixed summation order)
 //   anc_search   distance GEMM <z_a, z_t> by bf16 MFMA (the bf16 inputs are exact, the fp32
-//                accumulation is the only rounding) on 128-anchor x 256-token tiles; ranking
-//                key ||z_a||^2 - 2 <z_a, z_t> (||z_t||^2 is common to a token's candidates);
-//                each tile leaves every token's 4 best (key, anchor) pairs
+//                accumulation is the only rounding) on tiles of 256 x 256 or 128 anchors x 64
+//                tokens; ranking key ||z_a||^2 - 2 <z_a, z_t> (||z_t||^2 is common to a
+//                token's candidates); each tile leaves every token's 4 best (key, anchor) pairs
 //   anc_merge    a token's partial lists -> its 4 nearest anchors, nearest first (ties to the
 //                lower anchor number)
 //   anc_prep     coded salience gathered from the prefix's, residuals k_t - mean, v_t - mean
@@ -145,10 +145,10 @@ template <int SWAP> __device__ __forceinline__ void top4_lanes(Top4& t) {
 // 32 CF anchors), gemm_tile with the anchors as columns.  C[anchor][token]: lane -> token
 // column (lane % 16) and anchors 4 (lane / 16) + v of each 16-anchor tile, so a lane sorts 16
 // keys per token in registers, the four lanes of a token merge by lane swaps, the two anchor
-// halves through LDS.  Workgroups are mapped so that all anchor tiles of one token tile run on
-// the same XCD (its token rows stay in that XCD's L2).  Matrix-core bound; 32768-token Llama
-// layer (2046 anchors, 257 GFLOP): 508 us with 64 x 64 wave tiles and lists kept by insertion,
-// 250 us now (1030 TFLOP/s).
+// halves through LDS.  Workgroups are mapped so that an XCD takes consecutive token tiles of one
+// anchor tile, whose rows (1 MB) stay in its L2.  Matrix-core bound; 32768-token Llama layer
+// (2046 anchors, 257 GFLOP): 508 us with 64 x 64 wave tiles and lists kept by insertion, 250 us
+// now (1030 TFLOP/s).
 struct AnSearch {
     const uint16_t* K;
     const uint16_t* V;

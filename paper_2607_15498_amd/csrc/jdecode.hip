@@ -23,6 +23,7 @@
 // launches took 78 us.
 #include <type_traits>
 
+#include "vr_gemm.h"
 #include "vr_internal.h"
 
 namespace vr {
@@ -110,10 +111,6 @@ __device__ __forceinline__ void frag8(const Raw8<F32>& r, int nv, u32x4& hi, u32
 }
 
 typedef __attribute__((address_space(3))) uint8_t jd_lds;
-// One direct-to-LDS load: 16 bytes per lane from `src` to LDS byte address dst + 16 lane.
-__device__ __forceinline__ void jd_load(const void* src, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(dst) : "memory", "m0");
-}
 // waits until at most n (wave-uniform, >= 0; more than 8 counts as 8) of this wave's loads are in flight
 __device__ __forceinline__ void jd_wait(int n) {
     switch (n) {
@@ -269,7 +266,8 @@ __global__ __launch_bounds__(256) void jq_kernel(JDec p) {
 // each load took 100 cycles to issue).  A wave per slice and tile of 16 tokens, two tiles and one
 // barrier per step (8 waves and a tile per step: 20 us).  Operands are 16-byte LDS reads at any
 // 2-byte alignment; lanes past their row's end read nothing (18.2 against 20.2 us: LDS is what
-// binds, with the vector instructions).
+// binds, with the vector instructions).  fp32: the ring holds one tile per step (16 rows of 1024
+// are 64 KB), so the second eight waves only load; eight waves in all were not measured there.
 template <bool F32, int RT> struct JScore {
     static constexpr int NQ = 16 * RT;
     static constexpr int ES = F32 ? 4 : 2;
@@ -331,8 +329,8 @@ __global__ __launch_bounds__(JS_T, 4) void js_kernel(JDec p) {
         auto issue = [&](int to) {                 // own units before `to`
             for (; iu < to; iu += 16) {
                 const uint8_t* a = src + min((uint32_t)iu * 1024u + 16u * lane, end16);
-                jd_load(a, ring0 + 1024u * (uint32_t)slot);
-                if (slot == 0) jd_load(a, ring0 + RING);
+                gemm_load(a, ring0 + 1024u * (uint32_t)slot);
+                if (slot == 0) gemm_load(a, ring0 + RING);
                 slot += 16;
                 if (slot >= C::RU) slot -= C::RU;
             }

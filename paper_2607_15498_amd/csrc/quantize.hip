@@ -99,7 +99,7 @@ struct QzParams {
     const uint32_t* chunk_off;   // bf16 layout chunk bases (elements)
     const uint32_t* qchunk_off;  // quantised chunk bases (bytes)
     int64_t N, coef_stride, q_stride;
-    int G, bits;
+    int G;
 };
 
 // One workgroup per (chunk, head, stream), its wave w taking tiles w, w + 4, w + 8, w + 12.
@@ -175,13 +175,12 @@ template <int QB> __device__ __forceinline__ void qz_store(uint8_t* dst, const u
 }
 
 template <int QB>
-__global__ __launch_bounds__(64 * QZ_WAVES) void qz_kernel(QzParams p, int total) {
+__global__ __launch_bounds__(64 * QZ_WAVES) void qz_kernel(QzParams p) {
     constexpr int NT = 16 / QZ_WAVES;             // tiles per wave
     constexpr uint32_t INF16 = 0x7F80u;           // bf16 infinity's pattern
     __shared__ __attribute__((aligned(16))) float scl_s[QZ_WAVES][2][16];   // V: scales, reciprocals
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int item = blockIdx.x;                  // (chunk, head, stream)
-    if (item >= total) return;
     const int kv = item & 1;
     const int g = (item >> 1) % p.G;
     const int c = (item >> 1) / p.G;
@@ -341,13 +340,11 @@ hipError_t launch_quantize(const varrate_shape& sh, const varrate_cache& c, varr
     p.coef_stride = c.coef_stride;
     p.q_stride = q.q_stride;
     p.G = sh.G;
-    p.bits = q.bits;
-    const int total = n_chunks * sh.G * 2;                      // (chunk, head, stream)
-    const int grid = total;
+    const int grid = n_chunks * sh.G * 2;                       // (chunk, head, stream)
     switch (q.bits) {
-        case 3: qz_kernel<3><<<grid, 64 * QZ_WAVES, 0, st>>>(p, total); break;
-        case 4: qz_kernel<4><<<grid, 64 * QZ_WAVES, 0, st>>>(p, total); break;
-        case 8: qz_kernel<8><<<grid, 64 * QZ_WAVES, 0, st>>>(p, total); break;
+        case 3: qz_kernel<3><<<grid, 64 * QZ_WAVES, 0, st>>>(p); break;
+        case 4: qz_kernel<4><<<grid, 64 * QZ_WAVES, 0, st>>>(p); break;
+        case 8: qz_kernel<8><<<grid, 64 * QZ_WAVES, 0, st>>>(p); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

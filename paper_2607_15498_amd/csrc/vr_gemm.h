@@ -1,4 +1,5 @@
-// Tile product shared by the shared-basis projection and the nearest-anchor search (gfx950):
+// Tile product shared by the shared-basis projection and the nearest-anchor search (gfx950; its
+// direct-to-LDS load also serves the shared-basis decode):
 // C[column][token] = sum over Dz of col[c][k] z_t[k], bf16 MFMA with fp32 sums, in steps of 64
 // elements of z.
 //
@@ -11,10 +12,11 @@
 //       fragment reads (16 rows, one piece each) free of bank conflicts;
 //   FRAG: columns as bf16 hi and lo parts already in fragment order, contiguous per step.
 //
-// What bounds it: 64-byte requests (16 rows x 32 elements per load) cap the loads at about a
-// tenth of what the matrix cores can use: 620 TFLOP/s for 256 x 128 tiles of 30720 x 2048 x 2048,
-// 740 with the products left out.  Whole lines give 1460 with the products left out, 1440 with
-// the loads left out and 1230 together (a library's plain 8192^3 product: 1480).
+// What bounds it: 64-byte requests (16 rows x 32 elements per load) cap the loads at about half of
+// what the matrix cores can use: 620 TFLOP/s for 256 x 128 tiles of 30720 x 2048 x 2048, 740 with
+// the products left out.  Whole lines give 1460 with the products left out, 1440 with the loads
+// left out and 1230 together (a library's plain product of that size, second operand transposed
+// as here: 1325; of 8192^3: 1650).
 #pragma once
 #include "vr_device.h"
 
