@@ -147,8 +147,8 @@ template <int SWAP> __device__ __forceinline__ void top4_lanes(Top4& t) {
 // keys per token in registers, the four lanes of a token merge by lane swaps, the two anchor
 // halves through LDS.  Workgroups are mapped so that an XCD takes consecutive token tiles of one
 // anchor tile, whose rows (1 MB) stay in its L2.  Matrix-core bound; 32768-token Llama layer
-// (2046 anchors, 257 GFLOP): 508 us with 64 x 64 wave tiles and lists kept by insertion, 250 us
-// now (1030 TFLOP/s).
+// (2046 anchors, 257 GFLOP): 508 us with 64 x 64 wave tiles and lists kept by insertion, 252 us
+// now (1020 TFLOP/s; 2 us of it order NaN keys behind infinite ones).
 struct AnSearch {
     const uint16_t* K;
     const uint16_t* V;

@@ -18,9 +18,10 @@
 // Scores and values are two launches because a single pass leaves a record of NQ x R sums per
 // workgroup, 33.5 MB to write and read back for 26.7 MB of coefficients; values over 64 ranges
 // leave 8 MB, and the second read of the coefficients comes from the last-level cache.
-// Llama layer, 32768 tokens, R = 1024: 5.9 + 18.4 + 19.0 + 5.1 + 3.9 us; the single pass (47.7 us,
-// 16 consecutive tokens per step, one step's loads ahead) with its q', exact and three combining
-// launches took 78 us.
+// Llama layer, 32768 tokens, R = 1024: 49.7 us the call, the launches 6.2 + 18.2 + 18.9 + 5.0 +
+// 3.8 us in a kernel trace (which closes no gaps: they need not add up to the call); the single pass
+// (47.7 us in the trace, 16 consecutive tokens per step, one step's loads ahead) with its q', exact
+// and three combining launches took 74.6 us the call.
 #include <type_traits>
 
 #include "vr_gemm.h"
