@@ -533,8 +533,11 @@ hipError_t launch_anchor_search(const varrate_shape& sh, const void* K, const vo
     // anchors share it: narrow ones are the faster as long as two rounds of 512 hold them all.
     // Whole compressions with either shape forced, narrow / wide us: 4 KV heads 126 / 129 at 864
     // narrow tiles, 143 / 144 at 1020, 155 / 151 at 1080, 134 / 129 at 1134; 8 KV heads 142 / 148,
-    // 166 / 169, 178 / 169, 161 / 152
-    const bool wide = (Nc + 63) / 64 * ((na + 127) / 128) > 1024;
+    // 166 / 169, 178 / 169, 161 / 152.  Up to 256 anchors, one wide tile, nothing is read again from a
+    // cache and three quarters of the CUs have to load: 8 KV heads, 157 anchors, 295 / 306 at 156 wide
+    // tiles and 371 / 352 at 194; 98 anchors, one tile of either shape, 355 / 362 at 194
+    const int64_t t64 = (Nc + 63) / 64, t256 = (Nc + 255) / 256;
+    const bool wide = t64 * ((na + 127) / 128) > 1024 && (na > 256 || t256 >= 192);
     hipError_t e = wide ? launch_search<4, 8>(p, st) : launch_search<1, 4>(p, st);
     if (e != hipSuccess) return e;
     anc_merge<<<(unsigned)((Nc + 255) / 256), 256, 0, st>>>(w.part, Nc, p.n_atiles, nn);
