@@ -201,9 +201,9 @@ def test_joint_multi_sequence_appended(vr, oracle_lib, Q):
     (1, 1, 256, 99, 0), (63, 1, 256, 80, 0), (64, 2, 512, 90, 16), (65, 2, 256, 45, 1), (257, 2, 512, 60, 0),
     (12288, 1, 256, 30, 0), (12289, 2, 512, 20, 0), (12800, 1, 256, 70, 128)])
 def test_joint_projection_tile_edges(vr, N, G, R, kappa, r_min):
-    """The projection over token lists where its tiles and lists end: 64- and 256-token tiles one
-    short of, at and past a multiple, both sides of the switch between them, tokens of rank 0,
-    single coefficients.  Against Z W^T in 64 bits within the bound of the hi + lo basis and one
+    """The projection over token lists where its tiles and lists end: 64-token tiles one short of,
+    at and past a multiple (the 256-token ones below), tokens of rank 0, single coefficients.
+    Against Z W^T in 64 bits within the bound of the hi + lo basis and one
     storage rounding; nothing is written past the coded budget."""
     import torch
     w = 4
